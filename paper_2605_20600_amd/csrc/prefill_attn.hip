@@ -3,30 +3,40 @@
 // j <= i) V for the C prefix tokens of every (b, h), on the MFMA units of
 // gfx950.
 //
-// A block of 4 wavefronts takes 128 queries of one head, one wavefront per 32
-// of them.  The keys arrive in blocks of 128: the block's threads load one
-// into LDS together (K and V rows, padded by 16 bytes against bank conflicts)
-// with every load issued at once, so the head's keys cost one memory round
-// trip per 128 rather than one per 32-key tile and wavefront.  For each tile
-// of 32 keys at or before its queries, a wavefront computes
-//   S^T = K_tile Q^T   32x32x16 bf16 MFMAs over d (A = key rows from LDS,
-//                      B = the wavefront's query rows, held in registers), so
+// A block of W wavefronts takes W * 32 queries of one head, 32 each.  The keys
+// arrive in tiles of KT = 32 * SUBS: the K and V rows of the next tile go from
+// memory straight into LDS (global_load_lds, 16 bytes per lane) while the
+// current one is used, one barrier per tile.  The rows of a tile lie unpadded in LDS, their 16-byte
+// pieces permuted within the row (swizzle below) so that both operand reads
+// are free of bank conflicts.  For each tile a wavefront computes
+//   S^T = K_tile Q^T   32x32x16 bf16 MFMAs over d (A = key rows from LDS, B =
+//                      the wavefront's query rows, held in registers), so
 //                      that a lane holds 16 of the 32 scores of one query and
-//                      the other 16 sit in lane l ^ 32;
-//   online softmax     per query in fp32 (exp2 of pre-scaled scores), the
-//                      running max shared by the lane pair;
-//   O^T += V^T P^T     32x32x8 bf16 MFMAs: the score accumulators, rounded to
-//                      bf16, are exactly the B operand of this shape; each
-//                      lane reads its 4 keys of one dim from the LDS V rows.
+//                      32 keys, and the other 16 sit in lane l ^ 32;
+//   online softmax     per query in fp32 (exp2 of scaled scores);
+//   O^T += V^T P^T     32x32x16 bf16 MFMAs: the order of the 16 keys of a
+//                      step is free as long as both operands agree, so the
+//                      score accumulators, rounded to bf16, are the B operand
+//                      as they stand (slot 8 half + e: key 4 half + e for e <
+//                      4, else 8 + 4 half + e - 4), and the A operand takes
+//                      the same keys from the V rows by two transposing LDS
+//                      reads (ds_read_b64_tr_b16: four keys of one dim).
 // The normaliser sums the bf16-rounded weights that multiply V.  The same
 // launch stores the prefix keys and values into the cache (headkv_prefill):
-// the block of query tile t writes key block t from the registers it loaded
-// it into.  Prefixes shorter than 128 tokens, where most of a key block would
-// be clamped rows, take k_prefill_attn_tiles instead: each wavefront loads its
-// own 32-key tiles (the same MFMA steps).
+// each block writes the rows of its own queries from the tiles in LDS.
+//
+// Long prefixes are bound by the two MFMA chains of a wavefront and the
+// softmax between them (C = 2048, 64 heads of 128: 29 % of the matrix cores'
+// cycles, no LDS bank conflicts), short ones by the loads, then the stores, of
+// blocks that all run at once.  Per launch, with the tiles staged through
+// registers, V read four 2-byte elements at a time and 32x32x8 steps, and now:
+// C = 2048, 64 heads of 128 492 -> 102 us (674 TFLOP/s of causal products);
+// C = 300, 320 heads of 64 38.8 -> 21.7 us; C = 128, 256 heads of 128 18.4 ->
+// 15.3 us; C = 64, 512 heads of 128 20.3 -> 15.0 us (3.9 TB/s).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -40,343 +50,318 @@ namespace {
 using namespace dev;
 
 typedef short bf16x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-
-// fp32 -> bf16 bits, round to nearest even (finite inputs)
-__device__ __forceinline__ uint16_t bf16_rne(float x) {
-    const uint32_t u = __float_as_uint(x);
-    return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
 
 __device__ __forceinline__ bf16x8_t load8(const uint16_t* p) {
     const uint4 w = *reinterpret_cast<const uint4*>(p);
     return __builtin_bit_cast(bf16x8_t, w);
 }
 
-// grid: ceil(C / 128) x B*H blocks, the query tiles of a head adjacent;
-// block: 256 threads = 4 wavefronts of 32 queries
-// Each block also does Step 1's cache work for its head: the block of the
-// first query tile resets the head's layer state, and every block stores the
-// keys and values of its own 128 prefix rows into the cache.
+// Place of the 16-byte piece c of a tile row within that row: c ^ swizzle(row).
+// The 64 LDS banks hold one row of d = 128 or two of d = 64.  A K operand read
+// takes the same piece of 16 consecutive rows: the swizzle is a bijection of
+// the 16 rows (or pairs of rows) of a bank period, so they fall on 16 different
+// places.  A V operand read takes four adjacent pieces (32 dims) of 8 rows: the
+// top bits of the swizzle put four consecutive rows (pairs) on different
+// quarters of the banks.
 template <int D>
-__global__ __launch_bounds__(256) void k_prefill_attn_keys(LayerDev L, int nheads,
-                                                      const uint16_t* __restrict__ qc,
-                                                      const uint16_t* __restrict__ kc,
-                                                      const uint16_t* __restrict__ vc,
-                                                      float* __restrict__ out, int C,
-                                                      float qscale, int64_t seg_bytes,
-                                                      int dense_cap, int dense_chunks) {
-    constexpr int KS = D / 16;            // 32x32x16 steps over d
-    constexpr int MB = D / 32;            // 32-dim blocks of the output
-    constexpr int CH = D / 8;             // 16-byte pieces of a row
-    constexpr int PER = 128 * CH / 256;   // pieces of a 128-key block per thread (K or V)
-    constexpr int PITCH = D + 8;          // LDS row pitch in bf16
-    __shared__ __align__(16) uint16_t ks[128 * PITCH];
-    __shared__ __align__(16) uint16_t vs[128 * PITCH];
-    const int tiles = (C + 127) / 128;
-    const int bh = blockIdx.x / tiles;
-    const int tile = blockIdx.x - bh * tiles;
+__device__ __forceinline__ int swizzle(int row) {
+    return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : ((row & 2) << 1) | ((row >> 2) & 3);
+}
+
+// 16 bytes per lane from memory into LDS at dst + 16 * lane (dst: the
+// wavefront's, a byte offset in LDS).  As asm, since the compiler would wait
+// for the next tile's loads in front of this tile's reads; the caller waits
+// (lds_loads_done) before the barrier after which the tile is read.  Nothing
+// else here uses m0 (LDS instructions of gfx950 do not).
+__device__ __forceinline__ void load_to_lds(const uint16_t* src, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :
+                 : "v"(src), "s"(dst)
+                 : "memory");
+}
+__device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+template <int D, int W, int SUBS>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2)))
+void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
+                    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
+                    float* __restrict__ out, int C, float qscale, int64_t seg_bytes,
+                    int dense_cap, int dense_chunks) {
+    constexpr int KS = D / 16;           // 32x32x16 steps over d
+    constexpr int MB = D / 32;           // 32-dim blocks of the output
+    constexpr int CH = D / 8;            // 16-byte pieces of a row
+    constexpr int KT = 32 * SUBS;        // keys of a tile
+    constexpr int QT = 32 * W;      // queries of a block
+    constexpr int ROWB = 2 * D;          // bytes of a row
+    constexpr int NP = KT * CH / 64;     // 64-piece loads of a tile's K (or V)
+    extern __shared__ __align__(16) unsigned char lds[];  // [buffer][K, V][KT][D]
+    const int tiles = (C + QT - 1) / QT;
+    // the longest query tiles first; the tiles of a head are nheads blocks
+    // apart, so with a multiple of 8 heads they share an XCD's L2
+    const int tile = tiles - 1 - (int)blockIdx.x / nheads;
+    const int bh = (int)blockIdx.x % nheads;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     prefill_head(L, bh, nheads, C, D, kc, vc, seg_bytes, dense_cap, dense_chunks, 0, 0, tile == 0,
-                 threadIdx.x, 256);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int q0 = tile * 128 + wave * 32;
-    const bool active = q0 < C;  // a wavefront past C still loads and meets the barriers
+                 tid, 64 * W);
+    const int q0 = tile * QT + wave * 32;
     const int half = lane >> 5, j = lane & 31;  // j: this lane's query (and key row of a tile)
     const size_t base = (size_t)bh * C * D;
-    const uint16_t* Q = qc + base;
-    const uint4* K4 = reinterpret_cast<const uint4*>(kc + base);
-    const uint4* V4 = reinterpret_cast<const uint4*>(vc + base);
-    const int qrow = min(q0 + j, C - 1);
+    const uint16_t* K = kc + base;
+    const uint16_t* V = vc + base;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+    // a piece's place in its load is the lane's; the lane fetches the piece
+    // that belongs there.  Rows past C: row C - 1 again (finite, masked).
+    auto load_tile = [&](int kb, int buf) {
+#pragma unroll
+        for (int i0 = 0; i0 < NP; i0 += W) {
+            const int i = i0 + wave;
+            const int p = i * 64 + lane, row = p / CH, c = (p % CH) ^ swizzle<D>(row);
+            const size_t src = (size_t)min(kb * KT + row, C - 1) * D + c * 8;
+            const uint32_t dst = lds0 + (buf * 2 * KT) * ROWB + i * 1024;
+            load_to_lds(K + src, dst);
+            load_to_lds(V + src, dst + KT * ROWB);
+        }
+    };
+    const int nk = (min(C, (tile + 1) * QT) + KT - 1) / KT;  // key tiles of this block
+    load_tile(0, 0);
+    // up to two tiles: one round trip for both
+    if (nk == 2) load_tile(1, 1);
     bf16x8_t qb[KS];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) qb[s] = load8(Q + (size_t)qrow * D + 16 * s + 8 * half);
+    for (int s = 0; s < KS; ++s)
+        qb[s] = load8(qc + base + (size_t)min(q0 + j, C - 1) * D + 16 * s + 8 * half);
 
     f32x16_t acc[MB];
+    float m = -INFINITY, lsum = 0.f;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[mb][r] = 0.f;
-    float m = -INFINITY, lsum = 0.f;
-    const int q = q0 + j;  // this lane's query
     const SegPtrs cache = seg_ptrs(L.kv + (int64_t)bh * seg_bytes, C, dense_cap, D);
     uint4* cK = reinterpret_cast<uint4*>(cache.K);
     uint4* cV = reinterpret_cast<uint4*>(cache.V);
-    for (int kb = 0; kb <= tile; ++kb) {
-        // keys kb*128 .. kb*128 + 127 (rows past C clamped to C - 1: finite,
-        // and masked by the causal mask since every query is below C).  The
-        // barrier comes first, and every row is loaded and written: otherwise
-        // the compiler keeps the loaded rows in scratch memory, or sinks each
-        // load into the branch that uses it and waits for them one at a time.
-        if (kb > 0) __syncthreads();  // every wavefront is done with the previous block
-        uint4 kr[PER], vr[PER];
+    // this lane's part of the operand addresses: K row j, piece 2 s + half;
+    // V rows 4 half + (lane & 15) / 4 (and 8 on), dims 16 ((lane >> 4) & 1) +
+    // 4 (lane & 3) of a 32-dim block
+    const int l16 = lane & 15, vrow = 4 * half + (l16 >> 2);
+    const int vpiece = 2 * ((lane >> 4) & 1) + ((l16 & 3) >> 1);
+    constexpr int TILEB = 2 * KT * ROWB;  // bytes of a buffer, a power of two
+    typedef __attribute__((address_space(3))) bf16x8_t* lds8_t;
+    typedef __attribute__((address_space(3))) bf16x4_t* lds4_t;
+    uint32_t ka[KS], va[MB][2];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int c = tid + 256 * i, row = c / CH, col = c % CH;
-            const size_t key = (size_t)min(kb * 128 + row, C - 1);
-            kr[i] = K4[key * CH + col];
-            vr[i] = V4[key * CH + col];
-        }
-        // every load out before the first write: the empty asm makes the
-        // loaded values opaque, so that the register allocator cannot reload
-        // them one at a time next to their writes
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            asm volatile("" : "+v"(kr[i].x), "+v"(kr[i].y), "+v"(kr[i].z), "+v"(kr[i].w));
-            asm volatile("" : "+v"(vr[i].x), "+v"(vr[i].y), "+v"(vr[i].z), "+v"(vr[i].w));
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int c = tid + 256 * i, row = c / CH, col = c % CH;
-            *reinterpret_cast<uint4*>(ks + row * PITCH + col * 8) = kr[i];
-            *reinterpret_cast<uint4*>(vs + row * PITCH + col * 8) = vr[i];
-        }
-        if (kb == tile) {  // this block's own prefix rows into the cache
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int c = tid + 256 * i, row = c / CH, col = c % CH;
-                const int key = kb * 128 + row;
-                if (key < C) {
-                    cK[(size_t)key * CH + col] = kr[i];
-                    cV[(size_t)key * CH + col] = vr[i];
-                }
-            }
-        }
-        __syncthreads();
-        if (!active) continue;
-        for (int t = 0; t < 4; ++t) {
-            const int k0 = kb * 128 + 32 * t;
-            if (k0 > q0 + 31 || k0 >= C) break;  // causal: tiles at or before the queries
-            const uint16_t* kt = ks + (32 * t) * PITCH;
-            const uint16_t* vt = vs + (32 * t) * PITCH;
-            // S^T[key i][query j] for keys k0 .. k0 + 31
-            f32x16_t st;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) st[r] = 0.f;
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    *reinterpret_cast<const bf16x8_t*>(kt + j * PITCH + 16 * s + 8 * half), qb[s],
-                    st, 0, 0, 0);
-            // keys of accumulator r: k0 + 8 (r / 4) + 4 half + r % 4; causal mask
-            float mx = m;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = k0 + 8 * (r / 4) + 4 * half + (r & 3);
-                st[r] = key <= q ? st[r] * qscale : -INFINITY;
-                mx = fmaxf(mx, st[r]);
-            }
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float f = __builtin_amdgcn_exp2f(m - mx);  // m = -inf gives 0
-            m = mx;
-            lsum *= f;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mb][r] *= f;
-            // weights, rounded to bf16: B operands of the four 32x32x8 steps
-            bf16x4_t pb[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint16_t w = bf16_rne(__builtin_amdgcn_exp2f(st[4 * g + e] - mx));
-                    lsum += __uint_as_float((uint32_t)w << 16);
-                    pb[g][e] = (short)w;
-                }
-            // O^T[dim][query] += V^T[dim][key] P^T[key][query]
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    bf16x4_t va;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        va[e] = (short)vt[(8 * g + 4 * half + e) * PITCH + 32 * mb + j];
-                    acc[mb] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(va, pb[g], acc[mb], 0, 0, 0);
-                }
-        }
-    }
-    if (!active) return;
-    lsum += __shfl_xor(lsum, 32);
-    if (q >= C) return;
-    const float inv = 1.f / lsum;
-    float* o = out + base + (size_t)q * D;
-    // accumulator r of block mb: dim 32 mb + 8 (r / 4) + 4 half + r % 4
+    for (int s = 0; s < KS; ++s)
+        ka[s] = lds0 + j * ROWB + (((2 * s + half) ^ swizzle<D>(j)) << 4);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            float4 v;
-            v.x = acc[mb][4 * g] * inv;
-            v.y = acc[mb][4 * g + 1] * inv;
-            v.z = acc[mb][4 * g + 2] * inv;
-            v.w = acc[mb][4 * g + 3] * inv;
-            *reinterpret_cast<float4*>(o + 32 * mb + 8 * g + 4 * half) = v;
+        for (int i = 0; i < 2; ++i) {
+            const int row = vrow + 8 * i;
+            va[mb][i] = lds0 + KT * ROWB + row * ROWB + (l16 & 1) * 8 +
+                        (((4 * mb + vpiece) ^ swizzle<D>(row)) << 4);
         }
-}
 
-// A tile of 32 keys: the A operands of S^T (key row j, 16 dims per step, this
-// half's 8 of them) and 16-byte pieces of the V rows.
-template <int D>
-struct KeyTile {
-    bf16x8_t k[D / 16];
-    uint4 v[32 / (64 / (D / 8))];
-};
-
-template <int D>
-__device__ __forceinline__ KeyTile<D> load_tile(const uint16_t* K, const uint16_t* V, int t0, int j,
-                                                int half, int lane, int C) {
-    constexpr int LPR = D / 8, RPL = 64 / LPR;
-    KeyTile<D> t;
-    const int krow = min(t0 + j, C - 1);
+    // one tile: the scores against its keys, then, 32 keys at a time, the
+    // weights and their V rows
+    auto use_tile = [&](int kb) {
+        f32x16_t st[SUBS];
 #pragma unroll
-    for (int s = 0; s < D / 16; ++s) t.k[s] = load8(K + (size_t)krow * D + 16 * s + 8 * half);
+        for (int u = 0; u < SUBS; ++u)
 #pragma unroll
-    for (int i = 0; i < 32 / RPL; ++i) {
-        const int key = min(t0 + i * RPL + lane / LPR, C - 1);
-        t.v[i] = *reinterpret_cast<const uint4*>(V + (size_t)key * D + (lane % LPR) * 8);
-    }
-    return t;
-}
-
-// Prefixes shorter than 128 tokens (one query tile per head; most of a key
-// block would be clamped rows): each wavefront loads its own key tiles, one
-// at a time, the V tile through its own LDS rows.  Grid and block as for
-// k_prefill_attn_keys; the block copies its head's prefix rows into the cache.
-template <int D>
-__global__ __launch_bounds__(256) void k_prefill_attn_tiles(LayerDev L, int nheads,
-                                                      const uint16_t* __restrict__ qc,
-                                                      const uint16_t* __restrict__ kc,
-                                                      const uint16_t* __restrict__ vc,
-                                                      float* __restrict__ out, int C,
-                                                      float qscale, int64_t seg_bytes,
-                                                      int dense_cap, int dense_chunks) {
-    constexpr int KS = D / 16;  // 32x32x16 steps over d
-    constexpr int MB = D / 32;  // 32-dim blocks of the output
-    const int tiles = (C + 127) / 128;
-    const int bh = blockIdx.x / tiles;
-    const int tile = blockIdx.x - bh * tiles;
-    prefill_head(L, bh, nheads, C, D, kc, vc, seg_bytes, dense_cap, dense_chunks, tile * 128,
-                 min(C, tile * 128 + 128), tile == 0, threadIdx.x, 256);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int q0 = tile * 128 + wave * 32;
-    if (q0 >= C) return;
-    const int half = lane >> 5, j = lane & 31;  // j: this lane's query (and key row)
-    const size_t base = (size_t)bh * C * D;
-    const uint16_t* Q = qc + base;
-    const uint16_t* K = kc + base;
-    const uint16_t* V = vc + base;
-    const int qrow = min(q0 + j, C - 1);
-    bf16x8_t qb[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) qb[s] = load8(Q + (size_t)qrow * D + 16 * s + 8 * half);
-
-    f32x16_t acc[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mb][r] = 0.f;
-    float m = -INFINITY, lsum = 0.f;
-    const int q = q0 + j;                              // this lane's query
-    const int k_last = min(q0 + 31, C - 1);            // last key any query here sees
-    constexpr int LPR = D / 8;                         // lanes per V row (16 bytes each)
-    constexpr int RPL = 64 / LPR;                      // V rows per wavefront load
-    __shared__ __align__(16) uint16_t sv_all[4][32 * D];
-    uint16_t* sv = sv_all[wave];                       // this wavefront's V tile [key][dim]
-    for (int k0 = 0; k0 <= k_last; k0 += 32) {
-        const KeyTile<D> cur = load_tile<D>(K, V, k0, j, half, lane, C);
-        const bf16x8_t* kb = cur.k;
-        const uint4* vrow = cur.v;
-        // S^T[key i][query j] for keys k0 .. k0 + 31
-        f32x16_t st;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = 0.f;
+            for (int r = 0; r < 16; ++r) st[u][r] = 0.f;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
-            st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[s], qb[s], st, 0, 0, 0);
-        // keys of accumulator r: k0 + 8 (r / 4) + 4 half + r % 4; causal mask
-        float mx = m;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = k0 + 8 * (r / 4) + 4 * half + (r & 3);
-            st[r] = key <= q ? st[r] * qscale : -INFINITY;
-            mx = fmaxf(mx, st[r]);
+            for (int u = 0; u < SUBS; ++u)
+                st[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    ((lds8_t)(uintptr_t)ka[s])[2 * u * ROWB], qb[s], st[u], 0, 0, 0);
+        // four operand reads ahead of their use
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+        for (int i = 0; i < KS * SUBS - 4; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float f = __builtin_amdgcn_exp2f(m - mx);  // m = -inf gives 0
-        m = mx;
-        lsum *= f;
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+        if (kb * KT + KT - 1 > q0) {  // a tile on the diagonal: causal mask
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+            for (int u = 0; u < SUBS; ++u)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mb][r] *= f;
-        // weights, rounded to bf16: B operands of the four 32x32x8 steps
-        bf16x4_t pb[4];
+                for (int r = 0; r < 16; ++r) {
+                    const int key = kb * KT + 32 * u + 8 * (r / 4) + 4 * half + (r & 3);
+                    if (key > q0 + j) st[u][r] = -INFINITY;
+                }
+        }
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int u = 0; u < SUBS; ++u) {
+            float mx = st[u][0];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint16_t w = bf16_rne(__builtin_amdgcn_exp2f(st[4 * g + e] - mx));
-                lsum += __uint_as_float((uint32_t)w << 16);
-                pb[g][e] = (short)w;
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, st[u][r]);
+            // the other half of the query's keys is in lane l ^ 32
+            const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx),
+                                                            false, false);
+            mx = fmaxf(m, fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1])) * qscale);
+            if (__builtin_amdgcn_ballot_w64(mx != m) != 0) {
+                const float f = __builtin_amdgcn_exp2f(m - mx);  // m = -inf gives 0
+                m = mx;
+                lsum *= f;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[mb][r] *= f;
             }
-        // O^T[dim][query] += V^T[dim][key] P^T[key][query]; the wavefront's
-        // own LDS rows, so program order is the only ordering needed
+            // weights, rounded to bf16: the B operands of two steps
+            bf16x8_t pb[2];
 #pragma unroll
-        for (int i = 0; i < 32 / RPL; ++i)
-            *reinterpret_cast<uint4*>(sv + (i * RPL + lane / LPR) * D + (lane % LPR) * 8) = vrow[i];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                bf16x4_t va;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    va[e] = (short)sv[(8 * g + 4 * half + e) * D + 32 * mb + j];
-                acc[mb] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(va, pb[g], acc[mb], 0, 0, 0);
+            for (int r = 0; r < 16; r += 2) {
+                bf16x2_t p, one;
+                p[0] = (__bf16)__builtin_amdgcn_exp2f(fmaf(st[u][r], qscale, -m));
+                p[1] = (__bf16)__builtin_amdgcn_exp2f(fmaf(st[u][r + 1], qscale, -m));
+                one[0] = one[1] = (__bf16)1.f;
+                lsum = __builtin_amdgcn_fdot2_f32_bf16(p, one, lsum, false);
+                pb[r / 8][r % 8] = p[0];
+                pb[r / 8][r % 8 + 1] = p[1];
             }
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const int off = (32 * u + 16 * g) * ROWB / 8;
+                    const bf16x4_t a0 =
+                        __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(uintptr_t)va[mb][0] + off);
+                    const bf16x4_t a1 =
+                        __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(uintptr_t)va[mb][1] + off);
+                    const bf16x8_t a = __builtin_bit_cast(
+                        bf16x8_t, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
+                    acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[g], acc[mb], 0, 0, 0);
+                }
+        }
+    };
+    for (int kb = 0; kb < nk; ++kb) {
+        const int buf = kb & 1;
+        // this wavefront's loads of the tile are in, and after the barrier
+        // every wavefront's, and all are done with the other buffer
+        lds_loads_done();
+        __syncthreads();
+        if (nk > 2 && kb + 1 < nk) load_tile(kb + 1, buf ^ 1);
+        if ((kb + 1) * KT > tile * QT) {  // rows of this block's queries: into the cache
+#pragma unroll
+            for (int i0 = 0; i0 < NP; i0 += W) {
+                const int p = (i0 + wave) * 64 + lane, row = p / CH;
+                const int c = (p % CH) ^ swizzle<D>(row), key = kb * KT + row;
+                const uint4* src = reinterpret_cast<const uint4*>(lds + (buf * 2 * KT) * ROWB) + p;
+                if (key < C) {
+                    cK[(size_t)key * CH + c] = src[0];
+                    cV[(size_t)key * CH + c] = src[KT * CH];
+                }
+            }
+        }
+        if (q0 < C && kb * KT <= q0 + 31) use_tile(kb);  // keys at or before the queries
+        // the other buffer
+#pragma unroll
+        for (int s = 0; s < KS; ++s) ka[s] ^= TILEB;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            va[mb][0] ^= TILEB;
+            va[mb][1] ^= TILEB;
+        }
     }
-    lsum += __shfl_xor(lsum, 32);
-    if (q >= C) return;
-    const float inv = 1.f / lsum;
-    float* o = out + base + (size_t)q * D;
-    // accumulator r of block mb: dim 32 mb + 8 (r / 4) + 4 half + r % 4
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum),
+                                                    false, false);
+    const float inv = 1.f / (__uint_as_float(x[0]) + __uint_as_float(x[1]));
+    // accumulator r of block mb: dim 32 mb + 8 (r / 4) + 4 half + r % 4, i.e.
+    // piece 8 mb + 2 (r / 4) + half of the row's 16-byte pieces
+    auto piece = [&](int mb, int g) {
+        float4 v;
+        v.x = acc[mb][4 * g] * inv;
+        v.y = acc[mb][4 * g + 1] * inv;
+        v.z = acc[mb][4 * g + 2] * inv;
+        v.w = acc[mb][4 * g + 3] * inv;
+        return v;
+    };
+    constexpr int OP = D / 4;  // pieces of an output row
+    float4* o = reinterpret_cast<float4*>(out + base + (size_t)q0 * D);
+    if constexpr (D == 64) {
+        // through LDS (this wavefront's 32 rows, the pieces permuted within
+        // the row), so that whole rows leave together: C = 300, 320 heads 22.5
+        // -> 21.7 us.  At d = 128, where a row is 512 bytes, writing from the
+        // accumulators is 2 % faster (C = 64 and 128, 512 and 256 heads).
+        __syncthreads();  // every wavefront is done with the tiles
+        float4* ob = reinterpret_cast<float4*>(lds) + wave * 32 * OP;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            float4 v;
-            v.x = acc[mb][4 * g] * inv;
-            v.y = acc[mb][4 * g + 1] * inv;
-            v.z = acc[mb][4 * g + 2] * inv;
-            v.w = acc[mb][4 * g + 3] * inv;
-            *reinterpret_cast<float4*>(o + 32 * mb + 8 * g + 4 * half) = v;
+            for (int g = 0; g < 4; ++g)
+                ob[j * OP + ((8 * mb + 2 * g + half) ^ (j & (OP - 1)))] = piece(mb, g);
+#pragma unroll
+        for (int i = 0; i < OP / 2; ++i) {
+            const int row = (i * 64 + lane) / OP, c = lane & (OP - 1);
+            const float4 v = ob[row * OP + (c ^ (row & (OP - 1)))];
+            if (q0 + row < C) o[row * OP + c] = v;
         }
+    } else if (q0 + j < C) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) o[j * OP + 8 * mb + 2 * g + half] = piece(mb, g);
+    }
 }
 
 inline int last_error() { return (int)hipGetLastError(); }
+
+struct PrefillCall {
+    const LayerDev& L;
+    const Shape& s;
+    const uint16_t *qc, *kc, *vc;
+    float* out;
+    int64_t dense_seg_bytes;
+    int dense_cap, dense_chunks;
+    hipStream_t st;
+    hipEvent_t e0, e1;
+};
+
+template <int D, int W, int SUBS>
+void prefill_attn_launch(const PrefillCall& c) {
+    constexpr int QT = 32 * W, KT = 32 * SUBS;
+    const float qscale = (float)(1.4426950408889634 / std::sqrt((double)D));
+    const unsigned grid = (unsigned)((c.s.C + QT - 1) / QT) * (unsigned)c.s.BH;
+    const size_t tile_bytes = (size_t)2 * KT * D * sizeof(uint16_t);
+    const size_t out_bytes = D == 64 ? (size_t)32 * W * D * sizeof(float) : 0;
+    const size_t lds = std::max(tile_bytes * (c.s.C > KT ? 2 : 1), out_bytes);
+    hipExtLaunchKernelGGL((k_prefill_attn<D, W, SUBS>), dim3(grid), dim3(64 * W), lds, c.st,
+                          c.e0, c.e1, 0, c.L, c.s.BH, c.qc, c.kc, c.vc, c.out, c.s.C, qscale,
+                          c.dense_seg_bytes, c.dense_cap, c.dense_chunks);
+}
+
+// Wavefronts (of 32 queries) per block.  Four: the keys in LDS serve 128
+// queries (C = 300, 256 heads of 128: 29.9 us, with two 35.3, with one 61.0; C
+// = 2048, 64 heads: 103, 141 and 297).  Up to 128 tokens a head is one such
+// block, and with at most one head per CU half of it finds room beside each
+// other: two, twice as many blocks (C = 77 / 128, 256 heads: 10.2 / 12.6 ->
+// 9.2 / 12.2 us; with 512 heads two would be slower, 20.0 -> 25.4 us).  Up to
+// 64 (32) tokens two (one) hold all queries.
+template <int D>
+void prefill_attn_dispatch(const PrefillCall& c) {
+    const int C = c.s.C;
+    if (C <= 32) prefill_attn_launch<D, 1, 1>(c);
+    else if (C <= 64 || (C <= 128 && c.s.BH <= kCus)) prefill_attn_launch<D, 2, 2>(c);
+    else prefill_attn_launch<D, 4, 2>(c);
+}
 
 }  // namespace
 
 int launch_prefill_attn(const LayerDev& L, const Shape& s, const uint16_t* qc, const uint16_t* kc,
                         const uint16_t* vc, float* out, int64_t dense_seg_bytes, int dense_cap,
                         int dense_chunks, void* stream, void* ev_start, void* ev_stop) {
-    const dim3 grid((unsigned)((s.C + 127) / 128) * (unsigned)s.BH), block(256);
-    const float qscale = (float)(1.4426950408889634 / std::sqrt((double)s.d));
-    hipStream_t st = (hipStream_t)stream;
-    hipEvent_t e0 = static_cast<hipEvent_t>(ev_start), e1 = static_cast<hipEvent_t>(ev_stop);
-#define HEADKV_PREFILL_LAUNCH(KERNEL)                                                        \
-    hipExtLaunchKernelGGL(KERNEL, grid, block, 0, st, e0, e1, 0, L, s.BH, qc, kc, vc, out, s.C, \
-                          qscale, dense_seg_bytes, dense_cap, dense_chunks)
-    if (s.C >= 128) {
-        if (s.d == 128) HEADKV_PREFILL_LAUNCH(k_prefill_attn_keys<128>);
-        else HEADKV_PREFILL_LAUNCH(k_prefill_attn_keys<64>);
-    } else {
-        if (s.d == 128) HEADKV_PREFILL_LAUNCH(k_prefill_attn_tiles<128>);
-        else HEADKV_PREFILL_LAUNCH(k_prefill_attn_tiles<64>);
-    }
-#undef HEADKV_PREFILL_LAUNCH
+    const PrefillCall c{L, s, qc, kc, vc, out, dense_seg_bytes, dense_cap, dense_chunks,
+                        (hipStream_t)stream, static_cast<hipEvent_t>(ev_start),
+                        static_cast<hipEvent_t>(ev_stop)};
+    if (s.d == 128) prefill_attn_dispatch<128>(c);
+    else prefill_attn_dispatch<64>(c);
     return last_error();
 }
 
