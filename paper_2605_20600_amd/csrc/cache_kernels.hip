@@ -49,64 +49,164 @@ __global__ void k_append(LayerDev L, int C, int d, AppendArgs a) {
 }
 
 // ------------------------------------------------------------ head grouping
-__global__ __launch_bounds__(kBlock) void k_score(LayerDev L, int d, const uint16_t* q,
-                                                  int32_t* n_star, uint8_t* is_local, int len,
-                                                  double sqrt_d, double tau, int local_window) {
+// The in-order sums read the weights in groups of kScoreRun, a group ahead of
+// the additions: up to two groups before the first weight and past the last.
+constexpr int kScoreRun = 16;
+
+struct ScoreLds {
+    // tile rows of the wavefronts that have any | weights (f64, padded)
+    static size_t off_w(int len, int d, int r) {
+        const int per = 64 * r, waves = (len + per - 1) / per;
+        return (size_t)(waves < kBlock / 64 ? waves : kBlock / 64) * per * d * sizeof(uint16_t);
+    }
+    static size_t bytes(int len, int d, int r) {
+        return off_w(len, d, r) + sizeof(double) * ((size_t)len + 4 * kScoreRun);
+    }
+};
+
+// One block per head.  The normaliser and the backward mass are sums whose
+// order decides n*, so one thread adds each of them in order: the launch is
+// bound by those two chains of len dependent fp64 additions (3.2 and 4.4
+// of 15 us at 428 tokens) and by the round trips before them.  The reads of a chain go
+// out kScoreRun values ahead of their additions (read one by one, each behind
+// the LDS, the chains took three quarters of the launch), and the key rows
+// arrive in LDS as whole rows, all of a tile's loads in flight at once, R rows
+// per thread, so that a query value read from LDS serves R rows (read by the
+// threads from memory, 16 bytes of 64 rows at a time, one round trip each).
+// 256 heads of 428 tokens, d = 128: 41.3 -> 17 us.
+template <int D, int R>
+__global__ __launch_bounds__(kBlock) void k_score(LayerDev L, const uint16_t* q, int32_t* n_star,
+                                                  uint8_t* is_local, int len, double sqrt_d,
+                                                  double tau, int local_window, int w_off) {
 #pragma clang fp contract(off)
-    extern __shared__ double a[];  // [len]
-    __shared__ double qd[128];
+    constexpr int CH = D / 8, ROWB = 2 * D, PER = 64 * R;  // rows per wavefront and tile
+    extern __shared__ __align__(16) unsigned char lds[];
+    double* a = reinterpret_cast<double*>(lds + w_off) + 2 * kScoreRun;  // [len]
+    __shared__ __align__(16) double qd[D];
     __shared__ double red[kBlock / 64];
     __shared__ double zsh;
-    const int h = blockIdx.x, tid = threadIdx.x;
-    for (int i = tid; i < d; i += kBlock) qd[i] = bf_f64(q[(size_t)h * d + i]);
-    __syncthreads();
+    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint16_t* K = reinterpret_cast<const uint16_t*>(L.kv + L.seg_off[h]);
-    // logits q.k_j / sqrt(d), dims summed in order
+    const unsigned char* tile = lds + wave * PER * ROWB;
+    const uint32_t tile0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
+                           wave * PER * ROWB;
+    auto load_rows = [&](int r0) {  // this wavefront's rows, those past the end the last again
+#pragma unroll
+        for (int i = 0; i < R * CH; ++i) {
+            const int p = i * 64 + lane, row = p / CH, c = (p % CH) ^ swizzle<D>(row);
+            load_to_lds(K + (size_t)min(r0 + row, len - 1) * D + c * 8, tile0 + i * 1024);
+        }
+    };
+    int r0 = wave * PER;
+    if (r0 < len) load_rows(r0);
+    if (tid < D) qd[tid] = bf_f64(q[(size_t)h * D + tid]);
+    if (tid < 3 * kScoreRun) a[tid < kScoreRun ? len + tid : tid - 3 * kScoreRun] = 0.0;
+    __syncthreads();
+    // logits q.k_j / sqrt(d), dims summed in order; the product of two bf16
+    // values is exact in fp64, so an fma rounds like the multiply and the add
     double m = -INFINITY;
-    for (int j = tid; j < len; j += kBlock) {
-        const uint16_t* kr = K + (size_t)j * d;
-        double acc = 0.0;
-        for (int i = 0; i < d; i += 8) {
-            const Words<4> u = *reinterpret_cast<const Words<4>*>(kr + i);
+    for (; r0 < len; r0 += kBlock * R) {
+        lds_loads_done();
+        double acc[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = 0.0;
+#pragma unroll 4
+        for (int c = 0; c < CH; ++c) {
+            Words<4> u[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int row = 64 * r + lane;
+                u[r] = *reinterpret_cast<const Words<4>*>(tile + row * ROWB +
+                                                          ((c ^ swizzle<D>(row)) << 4));
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                acc = acc + qd[i + 2 * e] * (double)bf_lo(u.w[e]);
-                acc = acc + qd[i + 2 * e + 1] * (double)bf_hi(u.w[e]);
+                const double q0 = qd[8 * c + 2 * e], q1 = qd[8 * c + 2 * e + 1];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    acc[r] = fma(q0, (double)bf_lo(u[r].w[e]), acc[r]);
+                    acc[r] = fma(q1, (double)bf_hi(u[r].w[e]), acc[r]);
+                }
             }
         }
-        a[j] = acc / sqrt_d;
-        m = fmax(m, a[j]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int j = r0 + 64 * r + lane;
+            if (j >= len) continue;
+            const double l = acc[r] / sqrt_d;
+            a[j] = l;
+            m = fmax(m, l);
+        }
+        if (r0 + kBlock * R < len) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile has been read
+            load_rows(r0 + kBlock * R);
+        }
     }
     for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
-    if ((tid & 63) == 0) red[tid >> 6] = m;
+    if (lane == 0) red[wave] = m;
     __syncthreads();
     m = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
     for (int j = tid; j < len; j += kBlock) a[j] = exp(a[j] - m);
     __syncthreads();
-    if (tid == 0) {  // normaliser, summed over the cache in order
-        double z = 0.0;
-        for (int j = 0; j < len; ++j) z += a[j];
-        zsh = z;
+    if (wave == 0) {  // normaliser, summed over the cache in order (every lane the same)
+        double z = 0.0, t[kScoreRun];
+#pragma unroll
+        for (int i = 0; i < kScoreRun; ++i) t[i] = a[i];
+#pragma unroll 1
+        for (int j = 0; j < len; j += kScoreRun) {
+            double nx[kScoreRun];
+#pragma unroll
+            for (int i = 0; i < kScoreRun; ++i) nx[i] = a[j + kScoreRun + i];
+            __builtin_amdgcn_sched_barrier(0);
+            // (the zeros past the end do not change the sum)
+#pragma unroll
+            for (int i = 0; i < kScoreRun; ++i) z += t[i];
+#pragma unroll
+            for (int i = 0; i < kScoreRun; ++i) t[i] = nx[i];
+        }
+        if (tid == 0) zsh = z;
     }
     __syncthreads();
     const double z = zsh;
     for (int j = tid; j < len; j += kBlock) a[j] = a[j] / z;
     __syncthreads();
-    if (tid == 0) {  // mass accumulated backward from the newest token
-        double S = 0.0;
+    if (wave == 0) {  // mass accumulated backward from the newest token
+        const double* e = a + len - 1;
+        double S = 0.0, t[kScoreRun];
         int ns = len;
-        for (int nn = 1; nn <= len; ++nn) {
-            S += a[len - nn];
-            if (S >= tau) {
-                ns = nn;
+#pragma unroll
+        for (int i = 0; i < kScoreRun; ++i) t[i] = e[-i];
+#pragma unroll 1
+        for (int n0 = 0; n0 < len; n0 += kScoreRun) {
+            double nx[kScoreRun];
+#pragma unroll
+            for (int i = 0; i < kScoreRun; ++i) nx[i] = e[-(n0 + kScoreRun + i)];
+            __builtin_amdgcn_sched_barrier(0);
+            const double S0 = S;
+#pragma unroll
+            for (int i = 0; i < kScoreRun; ++i) S += t[i];
+            if (S >= tau) {  // reached in this group (the weights are not negative): where
+                double x = S0;
+                int n = 0;
+#pragma unroll
+                for (int i = 0; i < kScoreRun; ++i) {
+                    x += t[i];
+                    n += x >= tau ? 0 : 1;
+                }
+                ns = n0 + n + 1;
                 break;
             }
+#pragma unroll
+            for (int i = 0; i < kScoreRun; ++i) t[i] = nx[i];
         }
-        const int loc = ns < local_window ? 1 : 0;
-        n_star[h] = ns;
-        is_local[h] = (uint8_t)loc;
-        L.nstar[h] = ns;
-        L.label[h] = loc;
+        if (tid == 0) {
+            const int loc = ns < local_window ? 1 : 0;
+            n_star[h] = ns;
+            is_local[h] = (uint8_t)loc;
+            L.nstar[h] = ns;
+            L.label[h] = loc;
+        }
     }
 }
 
@@ -926,12 +1026,50 @@ int launch_append(const LayerDev& L, const Shape& s, const AppendArgs& a, void* 
     return last_error();
 }
 
+namespace {
+
+template <int D, int R>
+void score_launch(const LayerDev& L, const Shape& s, const uint16_t* q, int32_t* n_star,
+                  uint8_t* is_local, int len, double sqrt_d, double tau, int local_window,
+                  hipStream_t st) {
+    // allow more than 64 KB of dynamic LDS (gfx950: 160 KB), once per kernel
+    static const bool lds_ok = [] {
+        const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_score<D, R>),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            160 * 1024) == hipSuccess;
+        (void)hipGetLastError();
+        return ok;
+    }();
+    (void)lds_ok;
+    hipLaunchKernelGGL((k_score<D, R>), dim3(s.BH), dim3(kBlock), ScoreLds::bytes(len, D, R), st, L,
+                       q, n_star, is_local, len, sqrt_d, tau, local_window,
+                       (int)ScoreLds::off_w(len, D, R));
+}
+
+template <int D>
+void score_dispatch(const LayerDev& L, const Shape& s, const uint16_t* q, int32_t* n_star,
+                    uint8_t* is_local, int len, double sqrt_d, double tau, int local_window,
+                    hipStream_t st) {
+    // Two rows per thread while every head has a CU's LDS to itself and it
+    // holds them with the weights; one (half the LDS) when blocks share a CU or
+    // one row per thread covers the cache.
+    if (len > kBlock && s.BH <= kCus && ScoreLds::bytes(len, D, 2) <= kUpdateLdsBudget)
+        score_launch<D, 2>(L, s, q, n_star, is_local, len, sqrt_d, tau, local_window, st);
+    else
+        score_launch<D, 1>(L, s, q, n_star, is_local, len, sqrt_d, tau, local_window, st);
+}
+
+}  // namespace
+
 int launch_score(const LayerDev& L, const Shape& s, const uint16_t* q, int32_t* n_star,
                  uint8_t* is_local, int len, double sqrt_d, double tau, int local_window,
                  void* stream) {
-    hipLaunchKernelGGL(k_score, dim3(s.BH), dim3(kBlock), sizeof(double) * (size_t)len,
-                       (hipStream_t)stream, L, s.d, q, n_star, is_local, len, sqrt_d, tau,
-                       local_window);
+    if (s.d == 128)
+        score_dispatch<128>(L, s, q, n_star, is_local, len, sqrt_d, tau, local_window,
+                            (hipStream_t)stream);
+    else
+        score_dispatch<64>(L, s, q, n_star, is_local, len, sqrt_d, tau, local_window,
+                           (hipStream_t)stream);
     return last_error();
 }
 

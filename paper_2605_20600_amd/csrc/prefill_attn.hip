@@ -59,31 +59,6 @@ __device__ __forceinline__ bf16x8_t load8(const uint16_t* p) {
     return __builtin_bit_cast(bf16x8_t, w);
 }
 
-// Place of the 16-byte piece c of a tile row within that row: c ^ swizzle(row).
-// The 64 LDS banks hold one row of d = 128 or two of d = 64.  A K operand read
-// takes the same piece of 16 consecutive rows: the swizzle is a bijection of
-// the 16 rows (or pairs of rows) of a bank period, so they fall on 16 different
-// places.  A V operand read takes four adjacent pieces (32 dims) of 8 rows: the
-// top bits of the swizzle put four consecutive rows (pairs) on different
-// quarters of the banks.
-template <int D>
-__device__ __forceinline__ int swizzle(int row) {
-    return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : ((row & 2) << 1) | ((row >> 2) & 3);
-}
-
-// 16 bytes per lane from memory into LDS at dst + 16 * lane (dst: the
-// wavefront's, a byte offset in LDS).  As asm, since the compiler would wait
-// for the next tile's loads in front of this tile's reads; the caller waits
-// (lds_loads_done) before the barrier after which the tile is read.  Nothing
-// else here uses m0 (LDS instructions of gfx950 do not).
-__device__ __forceinline__ void load_to_lds(const uint16_t* src, uint32_t dst) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :
-                 : "v"(src), "s"(dst)
-                 : "memory");
-}
-__device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 template <int D, int W, int SUBS>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2)))
 void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
