@@ -160,8 +160,15 @@ Plan make_plan(const headkv_config& c) {
     return p;
 }
 
-// Block size of a chunk table for the given capacities: the fewest rounds of
-// resident blocks, then the largest blocks (fewest partial results).
+// Block size of a chunk table for the given capacities: the smallest whose
+// chunks are at most one per CU (the launch then waits for one short pass on
+// as many CUs as there are chunks, and the merge of a head's extra chunks
+// costs less than the longer pass: 32 heads of 250-450 tokens, d = 128, 256 /
+// 512 / 1024 threads 5.21 / 5.61 / 6.92 us per launch; 128 such heads, 7.73 /
+// 7.11 / 7.69, the 512-thread table is the smallest that fits; 4 heads 4.79 /
+// 5.22 / 6.25).  With more chunks than CUs at every size, the fewest rounds of
+// resident blocks, then the largest blocks (192 heads of up to 765 tokens, 512
+// / 1024 threads in one / two rounds: 11.8 / 15.7 us).
 int pick_chunk_threads(int C, int d, const std::vector<int>& cap) {
     int best = kAttnMaxThreads;
     long long best_rounds = -1;
@@ -170,7 +177,7 @@ int pick_chunk_threads(int C, int d, const std::vector<int>& cap) {
         for (int x : cap) items += chunks_of(C, x, t, d);
         const long long slots = attn_resident_blocks(t);
         const long long rounds = (items + slots - 1) / slots;
-        if (best_rounds < 0 || rounds < best_rounds) {
+        if (best_rounds < 0 || rounds < best_rounds || items <= kCus) {
             best = t;
             best_rounds = rounds;
         }
