@@ -258,29 +258,41 @@ struct UpdateLds {
     // eight rows (read eight at a time)
     static __host__ __device__ int stage_steps(int P) { return ((P < kRingChunk ? P : kRingChunk) + 7) & ~7; }
     // bitmap | word prefix | order (u16) | evict (u8) | positions (i32) |
-    // scores (f64, also two int lists) | query sum (f64 [d]), or with
-    // attention-sum scores G queries (f64 [G][d]) | with Eq. 6 scores: ring
-    // rows of the window staged for its sum (bf16 [min(P, kRingChunk)][d]);
-    // with attention-sum scores: weights of the cache for each query of a
-    // group (f64 [G][C + cap])
+    // scores (f64, also two int lists) | with Eq. 6 scores and with
+    // attention-sum scores of one query at a time: query (sum) (f64 [d]) |
+    // with Eq. 6 scores: ring rows of the window staged for its sum (bf16
+    // [min(P, kRingChunk)][d]); with attention-sum scores: weights of the cache
+    // for each of the g queries of a group (f64 [g][C + cap], for groups with
+    // weight_stride between the queries, and read kScoreRun * 2 past the end)
     static __host__ __device__ size_t off_wpre(int N) { return a16(4 * (size_t)words(N)); }
     static __host__ __device__ size_t off_order(int N) { return off_wpre(N) + a16(4 * (size_t)words(N)); }
     static __host__ __device__ size_t off_evict(int N, int cap) { return off_order(N) + a16(2 * (size_t)cap); }
     static __host__ __device__ size_t off_pos(int N, int cap) { return off_evict(N, cap) + a16((size_t)cap); }
     static __host__ __device__ size_t off_sig(int N, int cap) { return off_pos(N, cap) + a16(4 * (size_t)cap); }
     static __host__ __device__ size_t off_qs(int N, int cap) { return off_sig(N, cap) + a16(8 * (size_t)cap); }
-    static __host__ __device__ size_t off_w(int N, int cap, int d, int g) {
-        return off_qs(N, cap) + a16(8 * (size_t)d * g);
+    static __host__ __device__ size_t off_w(int N, int cap, int d) {
+        return off_qs(N, cap) + a16(8 * (size_t)d);
+    }
+    // doubles between the weights of a group's queries: 4 more than a multiple
+    // of the 32 doubles that the LDS banks hold, so that the 16 lanes that write
+    // (or, in the normalisers, read) one row's weights fall on different banks
+    // two at a time, the least for 16 doubles in steps of 4
+    static __host__ __device__ int weight_stride(int C, int cap) {
+        return (C + cap + 27) / 32 * 32 + 4;
     }
     static __host__ __device__ size_t bytes(int N, int cap, int d, int C, bool attn, int g, int P) {
-        return off_w(N, cap, d, attn ? g : 1) +
-               (attn ? a16(8 * (size_t)g * ((size_t)C + cap)) : a16(2 * (size_t)d * stage_steps(P)));
+        if (attn && g > 1)
+            return off_qs(N, cap) + 8 * ((size_t)g * weight_stride(C, cap) + 2 * kScoreRun);
+        return off_w(N, cap, d) +
+               (attn ? a16(8 * ((size_t)C + cap)) : a16(2 * (size_t)d * stage_steps(P)));
     }
 };
 
-// Window queries scored together by the attention-sum variant: up to 8 when
-// the period and the LDS allow, else one at a time.
-constexpr int kQueryGroup = 8;
+// Window queries scored together by the attention-sum variant: a group of up
+// to 16 (the columns of an fp64 MFMA) when the period and the LDS allow at
+// least 8, else one at a time.
+constexpr int kQueryGroup = 16;
+constexpr int kMinQueryGroup = 8;
 
 // fp64 score -> unsigned key with the same order (-0 and +0 map to one key,
 // since they compare equal).
@@ -426,176 +438,245 @@ __device__ __forceinline__ double dot_row(const double* qd, const uint16_t* row)
 // prefix rows, then the retained tokens with position <= p in position order
 // -- with logits q.k / sqrt(d) in fp64 and exp(l - max) summed in that order;
 // sig[r] for the history ranks [r_lo, r_hi) accumulates the weights query by
-// query, in step order.
-// The window is taken G queries at a time: each thread reads a cached row once
-// and runs the G dot products as G independent fp64 chains (dims in order);
-// the G normalisers are summed by G threads at once, each over its query's
-// cache in order.  qd: LDS [D][G]; w: LDS [G][wst] with wst >= C + n.
-template <int D, int G>
-__device__ void attention_sum_scores(const LayerDev& L, const SegPtrs& S, int C, int h, int n,
-                                     int r_lo, int r_hi, int step,
-                                     const uint16_t* order, const int32_t* pos, double* qd,
-                                     double* sig, double* w, int wst, double sqrt_d, int tid) {
+// query, in step order.  The product of two bf16 values is exact in fp64, so
+// an fma rounds exactly like the oracle's multiply and add.
+
+// The number of visual tokens that query p sees: ranks with position <= p.
+__device__ __forceinline__ int visible(const uint16_t* order, const int32_t* pos, int n, int p) {
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (pos[order[mid]] <= p) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// w[0] + w[1] + ... + w[len - 1] in order, the reads a group ahead of the
+// additions (up to 2 * kScoreRun - 1 doubles past the end are read).  common:
+// at most every lane's len, the same in all lanes (no lane checks its end
+// before it).
+__device__ __forceinline__ double sum_in_order(const double* w, int len, int common) {
 #pragma clang fp contract(off)
-    constexpr int WAVES = kBlock / 64;
-    __shared__ double red[WAVES][G];
-    __shared__ double msh[G], zsh[G];
-    __shared__ int nvs[G];
+    double z = 0.0, t[kScoreRun];
+#pragma unroll
+    for (int i = 0; i < kScoreRun; ++i) t[i] = w[i];
+    int j = 0;
+#pragma unroll 1
+    for (; j + kScoreRun <= common; j += kScoreRun) {
+        double nx[kScoreRun];
+#pragma unroll
+        for (int i = 0; i < kScoreRun; ++i) nx[i] = w[j + kScoreRun + i];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kScoreRun; ++i) z += t[i];
+#pragma unroll
+        for (int i = 0; i < kScoreRun; ++i) t[i] = nx[i];
+    }
+    for (; j < len; ++j) z += w[j];
+    return z;
+}
+
+// One query at a time (periods shorter than a group, caches whose weights for
+// a group do not fit the LDS).  qd: LDS [D]; w: LDS [C + n].
+template <int D, int NT>
+__device__ void attention_sum_single(const LayerDev& L, const SegPtrs& S, int C, int h, int n,
+                                     int r_lo, int r_hi, int step, const uint16_t* order,
+                                     const int32_t* pos, double* qd, double* sig, double* w,
+                                     double sqrt_d, int tid) {
+#pragma clang fp contract(off)
+    constexpr int WAVES = NT / 64;
+    __shared__ double red[WAVES];
+    __shared__ double zsh;
     const int P = L.ring_len;
     const int p0 = step - P + 1 > 0 ? step - P + 1 : 0;
     const int lane = tid & 63, wave = tid >> 6;
-    for (int r = r_lo + tid; r < r_hi; r += kBlock) sig[r] = 0.0;
-    for (int pa = p0; pa <= step; pa += G) {
-        const int ng = step + 1 - pa < G ? step + 1 - pa : G;  // queries of this group
-        // the group's queries in fp64 (rows past ng are zero and unused)
-        for (int i = tid; i < G * D; i += kBlock) {
-            const int g = i / D, e = i - g * D;
-            qd[e * G + g] = g < ng ? bf_f64(L.qring[((size_t)h * P + (pa + g) % P) * D + e]) : 0.0;
-        }
-        if (tid < ng) {  // visible visual tokens of query pa + tid: ranks with position <= p
-            const int p = pa + tid;
-            int lo = 0, hi = n;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (pos[order[mid]] <= p) lo = mid + 1; else hi = mid;
-            }
-            nvs[tid] = lo;
-        }
+    for (int r = r_lo + tid; r < r_hi; r += NT) sig[r] = 0.0;
+    for (int p = p0; p <= step; ++p) {
+        for (int i = tid; i < D; i += NT) qd[i] = bf_f64(L.qring[((size_t)h * P + p % P) * D + i]);
+        const int nv = visible(order, pos, n, p), len = C + nv;
         __syncthreads();
-        int vis[G];  // cache length seen by each query (non-decreasing in g)
-#pragma unroll
-        for (int g = 0; g < G; ++g) vis[g] = C + nvs[g < ng ? g : ng - 1];
-        const int rows = vis[G - 1];
-        // logits of every visible row for all queries of the group, and maxima
-        double m[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) m[g] = -INFINITY;
-        for (int j = tid; j < rows; j += kBlock) {
+        double m = -INFINITY;
+        for (int j = tid; j < len; j += NT) {
             const uint16_t* row =
                 j < C ? S.K + (size_t)j * D : S.K + (size_t)(C + order[j - C]) * D;
-            const uint4* kr = reinterpret_cast<const uint4*>(row);
-            // the queries are read from LDS for every row: an offset of zero
-            // the compiler cannot see through keeps it from hoisting all G x D
-            // of them out of the loop
-            int zo;
-            asm volatile("s_mov_b32 %0, 0" : "=s"(zo));
-            const double* qz = qd + zo;
-            // qz is dim-major ([D][G]): the query values of the next S dims are
-            // read while this S dims' products are added (a scheduling barrier
-            // keeps the reads a stage ahead).  The product of two bf16 values
-            // is exact in fp64, so an fma rounds exactly like the oracle's
-            // multiply and add.
-            constexpr int S = 4;
-            double acc[G], qa[S][G], qb[S][G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) acc[g] = 0.0;
-#pragma unroll
-            for (int e = 0; e < S; ++e)
-#pragma unroll
-                for (int g = 0; g < G; ++g) qa[e][g] = qz[e * G + g];
-            constexpr int HR = D / 16;  // half a row in flight at a time
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                uint4 v[HR];
-#pragma unroll
-                for (int c = 0; c < HR; ++c) v[c] = kr[half * HR + c];
-#pragma unroll
-                for (int c = 0; c < HR; ++c) {
-                    const uint32_t wv[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
-#pragma unroll
-                    for (int st = 0; st < 8 / S; ++st) {
-                        const int i0 = 8 * (half * HR + c) + st * S;  // first dim of the stage
-                        if (i0 + S < D) {
-#pragma unroll
-                            for (int e = 0; e < S; ++e)
-#pragma unroll
-                                for (int g = 0; g < G; ++g) qb[e][g] = qz[(i0 + S + e) * G + g];
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                        for (int e = 0; e < S; ++e) {
-                            const int k = st * S + e;  // dim within the 16-byte chunk
-                            const double kv =
-                                (double)((k & 1) ? bf_hi(wv[k / 2]) : bf_lo(wv[k / 2]));
-#pragma unroll
-                            for (int g = 0; g < G; ++g) acc[g] = fma(qa[e][g], kv, acc[g]);
-                        }
-#pragma unroll
-                        for (int e = 0; e < S; ++e)
-#pragma unroll
-                            for (int g = 0; g < G; ++g) qa[e][g] = qb[e][g];
-                    }
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const double l = acc[g] / sqrt_d;
-                w[(size_t)g * wst + j] = l;
-                if (j < vis[g]) m[g] = fmax(m[g], l);
-            }
+            const double l = dot_row<D>(qd, row) / sqrt_d;
+            w[j] = l;
+            m = fmax(m, l);
         }
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            for (int o = 32; o > 0; o >>= 1) m[g] = fmax(m[g], __shfl_xor(m[g], o));
-            if (lane == 0) red[wave][g] = m[g];
-        }
+        for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+        if (lane == 0) red[wave] = m;
         __syncthreads();
-        if (tid < G) {
-            double mx = red[0][tid];
-            for (int i = 1; i < WAVES; ++i) mx = fmax(mx, red[i][tid]);
-            msh[tid] = mx;
-        }
+        m = red[0];
+        for (int i = 1; i < WAVES; ++i) m = fmax(m, red[i]);
+        for (int j = tid; j < len; j += NT) w[j] = exp(w[j] - m);
         __syncthreads();
-        for (int j = tid; j < rows; j += kBlock)
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-                if (j < vis[g]) w[(size_t)g * wst + j] = exp(w[(size_t)g * wst + j] - msh[g]);
-        __syncthreads();
-        if (tid < ng) {  // normaliser of query pa + tid, summed over its cache in order
-            const double* wg = w + (size_t)tid * wst;
-            const int len = C + nvs[tid];
+        if (tid == 0) {  // normaliser, summed over the query's cache in order
             double z = 0.0;
             int j = 0;
             // the reads go out eight at a time, the additions stay in order
             for (; j + 8 <= len; j += 8) {
                 double t[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t[u] = wg[j + u];
+                for (int u = 0; u < 8; ++u) t[u] = w[j + u];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) z += t[u];
             }
-            for (; j < len; ++j) z += wg[j];
-            zsh[tid] = z;
+            for (; j < len; ++j) z += w[j];
+            zsh = z;
         }
         __syncthreads();
-        for (int r = r_lo + tid; r < r_hi; r += kBlock) {
+        const double z = zsh;
+        for (int r = r_lo + tid; r < r_hi && r < nv; r += NT) sig[r] = sig[r] + w[C + r] / z;
+        __syncthreads();  // qd, w, red and zsh are rewritten for the next query
+    }
+}
+
+// Element 4 t + kk of the 8 bf16 values of a 16-byte piece (kk = 0..3 by lane,
+// t constant), in fp64.
+__device__ __forceinline__ double piece_f64(const Words<4>& v, int t, int kk) {
+    const uint32_t u = (kk & 2) ? v.w[2 * t + 1] : v.w[2 * t];
+    return (double)((kk & 1) ? bf_hi(u) : bf_lo(u));
+}
+
+// G <= 16 queries at a time: the logits of 16 cache rows for all of them on
+// the fp64 matrix cores (v_mfma_f64_16x16x4: A = 16 rows x 4 dims, B = 4 dims x
+// 16 queries), D/4 steps that add the dims in order: a step rounds like four
+// fused multiply-adds in order of its dims (checked bit for bit against fma
+// chains on the GPU), so the logits are those of the scalar loop.  The G
+// normalisers are summed by G lanes at once, each over its query's cache in
+// order.  Bound by the fp64 rate (the vector ALU's too): on the vector ALU,
+// with the query values read from LDS for every row, the LDS reads took 4 times
+// the products (128 heads of up to 1,000 tokens, 65 queries of 128 dims: 395 ->
+// 204 us per update launch; in the slowest blocks the logits take 81 us, the
+// in-order sums 29, the exponentials 19).  w: LDS [G][wst] with wst >= C + n.
+template <int D, int NT>
+__device__ void attention_sum_group(const LayerDev& L, const SegPtrs& S, int C, int h, int n,
+                                    int r_lo, int r_hi, int step, const uint16_t* order,
+                                    const int32_t* pos, double* sig, double* w, int wst, int G,
+                                    double sqrt_d, int tid) {
+#pragma clang fp contract(off)
+    typedef double f64x4_t __attribute__((ext_vector_type(4)));
+    constexpr int WAVES = NT / 64, CH = D / 8;
+    __shared__ double red[WAVES][kQueryGroup];
+    __shared__ double msh[kQueryGroup], zsh[kQueryGroup];
+    __shared__ int nvs[kQueryGroup];
+    const int P = L.ring_len;
+    const int p0 = step - P + 1 > 0 ? step - P + 1 : 0;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, kk = lane >> 4;  // operand row or column, dim of a step
+    for (int r = r_lo + tid; r < r_hi; r += NT) sig[r] = 0.0;
+    // the keys of this wavefront's first 16 rows, the same for every group: each
+    // group's last rows leave them behind in kv (rows past the group's are
+    // computed and not used)
+    auto row_ptr = [&](int j) {
+        j = j < C + n ? j : C + n - 1;
+        const int visual = C + order[j < C ? 0 : j - C];
+        const int slot = j < C ? j : visual;
+        return reinterpret_cast<const Words<4>*>(S.K + (size_t)slot * D);
+    };
+    Words<4> kv[CH];
+    {
+        const Words<4>* kr = row_ptr(wave * 16 + col);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) kv[c] = kr[c];
+    }
+    for (int pa = p0; pa <= step; pa += G) {
+        const int ng = step + 1 - pa < G ? step + 1 - pa : G;  // queries of this group
+        if (tid < ng) nvs[tid] = visible(order, pos, n, pa + tid);
+        // B: query col (past ng the last one again, unused), dims 4 s + kk
+        double qb[D / 4];
+        {
+            const Words<4>* qr = reinterpret_cast<const Words<4>*>(
+                L.qring + ((size_t)h * P + (pa + (col < ng ? col : ng - 1)) % P) * D);
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const Words<4> v = qr[c];
+                qb[2 * c] = piece_f64(v, 0, kk);
+                qb[2 * c + 1] = piece_f64(v, 1, kk);
+            }
+        }
+        __syncthreads();
+        const int rows = C + nvs[ng - 1];  // seen by the last query, the most
+        const int vis = col < ng ? C + nvs[col] : 0;
+        // logits of every visible row for all queries of the group, and maxima
+        double m = -INFINITY;
+        for (int j0 = wave * 16; j0 < rows; j0 += 16 * WAVES) {
+            // each piece's place takes the next rows' piece as soon as it is used
+            // (the barriers keep the loads there, a whole pass ahead of their use)
+            const int jn = j0 + 16 * WAVES;
+            const Words<4>* nx = row_ptr((jn < rows ? jn : wave * 16) + col);
+            f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const double a0 = piece_f64(kv[c], 0, kk), a1 = piece_f64(kv[c], 1, kk);
+                kv[c] = nx[c];
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, qb[2 * c], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, qb[2 * c + 1], acc, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // accumulator r: row j0 + kk + 4 r, query col
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int j = j0 + kk + 4 * r;
+                if (j >= vis) continue;
+                const double l = acc[r] / sqrt_d;
+                w[(size_t)col * wst + j] = l;
+                m = fmax(m, l);
+            }
+        }
+        m = fmax(m, __shfl_xor(m, 16));
+        m = fmax(m, __shfl_xor(m, 32));
+        if (kk == 0) red[wave][col] = m;
+        __syncthreads();
+        if (tid < ng) {
+            double mx = red[0][tid];
+            for (int i = 1; i < WAVES; ++i) mx = fmax(mx, red[i][tid]);
+            msh[tid] = mx;
+        }
+        __syncthreads();
+        for (int g = 0; g < ng; ++g) {
+            const int len = C + nvs[g];
+            const double mg = msh[g];
+            double* wg = w + (size_t)g * wst;
+            for (int j = tid; j < len; j += NT) wg[j] = exp(wg[j] - mg);
+        }
+        __syncthreads();
+        if (tid < ng) zsh[tid] = sum_in_order(w + (size_t)tid * wst, C + nvs[tid], C + nvs[0]);
+        __syncthreads();
+        for (int r = r_lo + tid; r < r_hi; r += NT) {
             double a = sig[r];
             for (int g = 0; g < ng; ++g)
                 if (r < nvs[g]) a = a + w[(size_t)g * wst + C + r] / zsh[g];
             sig[r] = a;
         }
-        __syncthreads();  // qd, w, nvs, msh and zsh are rewritten for the next group
+        __syncthreads();  // w, nvs, red, msh and zsh are rewritten for the next group
     }
 }
 
+// How global heads are scored: Eq. 6; attention sums, one query or a group of
+// them at a time.  Separate instantiations.
+constexpr int kScoresMeanLogit = 0, kScoresAttnSingle = 1, kScoresAttnGroup = 2;
+
 // One block per head: optional append, then the periodic update of Eqs. 2-6
 // (or, with `relayout`, the first update fused with the move into the head's
-// new segment).  ATTN_SUM: the attention-sum scores instead of Eq. 6; a
-// separate instantiation, since its fp64 exp needs about twice the registers
-// (the Eq. 6 kernel stays under 64 VGPRs: eight 256-thread blocks per CU).
+// new segment).  SCORES: the attention-sum scores (group: queries at a time)
+// are separate instantiations, since their fp64 exp and matrix operands need
+// more registers (the Eq. 6 kernel stays under 64 VGPRs: eight 256-thread
+// blocks per CU).
 // The update of head h by the block's NT threads (body of k_update and of the
 // fused update + attention kernel); returns the head's length afterwards.
 // FUSED: the block goes on to the attention, so it has the attention's 128
 // VGPRs: where no K row was loaded ahead, a whole row is scored per round
 // trip instead of half of one.
-template <int D, bool ATTN_SUM, int G, int NT = kBlock, bool FUSED = false>
+template <int D, int SCORES, int NT = kBlock, bool FUSED = false>
 __device__ __forceinline__ int update_block(const LayerDev& L, int C, int N, const AppendArgs& a,
                                             const char* src_kv, int relayout,
                                             int64_t dense_seg_bytes, int dense_cap,
                                             int recent_len, int rs_num, int rs_den, int u,
-                                            int step, int lds_cap, double sqrt_d, int h) {
+                                            int step, int lds_cap, double sqrt_d, int group,
+                                            int h) {
 #pragma clang fp contract(off)
-    static_assert(!ATTN_SUM || NT == kBlock, "attention-sum scores run in 256-thread blocks");
+    constexpr bool ATTN_SUM = SCORES != kScoresMeanLogit;
     static_assert(NT >= 256 && NT % 64 == 0, "the radix select needs at least 256 threads");
     constexpr int kRow16 = D / 8;  // 16-byte chunks per row
     extern __shared__ __align__(16) unsigned char lds[];
@@ -763,11 +844,13 @@ __device__ __forceinline__ int update_block(const LayerDev& L, int C, int N, con
             const bool sel_near = m_near > 0 && m_near < n_near;
             const int r_lo = sel_long ? 0 : n_long;
             const int r_hi = sel_near ? T : n_long;
-            if (ATTN_SUM) {
-                attention_sum_scores<D, G>(
+            if constexpr (SCORES == kScoresAttnGroup) {
+                attention_sum_group<D, NT>(L, S, C, h, n, r_lo, r_hi, step, order, pos, sig, qs,
+                                           UpdateLds::weight_stride(C, lds_cap), group, sqrt_d, tid);
+            } else if constexpr (SCORES == kScoresAttnSingle) {
+                attention_sum_single<D, NT>(
                     L, S, C, h, n, r_lo, r_hi, step, order, pos, qs, sig,
-                    reinterpret_cast<double*>(lds + UpdateLds::off_w(N, lds_cap, D, G)),
-                    C + lds_cap, sqrt_d, tid);
+                    reinterpret_cast<double*>(lds + UpdateLds::off_w(N, lds_cap, D)), sqrt_d, tid);
             } else {
             // Eq. (6): mean raw logit of the past-P queries; the positive factor
             // 1/(P sqrt(d)) is dropped, the order is that of (sum q) . k, summed
@@ -778,7 +861,7 @@ __device__ __forceinline__ int update_block(const LayerDev& L, int C, int N, con
             // above) are staged through LDS, then each of D threads adds its
             // dim's column
             {
-                uint16_t* stage = reinterpret_cast<uint16_t*>(lds + UpdateLds::off_w(N, lds_cap, D, 1));
+                uint16_t* stage = reinterpret_cast<uint16_t*>(lds + UpdateLds::off_w(N, lds_cap, D));
                 double qacc = 0.0;
                 for (int c0 = w0; c0 <= wlast; c0 += kRingChunk) {
                     const int cn = wlast + 1 - c0 < kRingChunk ? wlast + 1 - c0 : kRingChunk;
@@ -948,17 +1031,18 @@ __device__ __forceinline__ int update_block(const LayerDev& L, int C, int N, con
     return n_new;
 }
 
-// NT threads per block: 256 with more heads than CUs (eight blocks per CU),
-// 1024 when each head has a CU to itself.
-template <int D, bool ATTN_SUM, int G, int NT>
+// NT threads per block: with Eq. 6 scores, 256 with more heads than CUs (eight
+// blocks per CU), 1024 when each head has a CU to itself; attention-sum groups,
+// 256 and 512 (two wavefronts per SIMD with their 256 VGPRs).
+template <int D, int SCORES, int NT>
 __global__ __launch_bounds__(NT) void k_update(LayerDev L, int C, int N, AppendArgs a,
                                                const char* src_kv, int relayout,
                                                int64_t dense_seg_bytes, int dense_cap,
                                                int recent_len, int rs_num, int rs_den, int u,
-                                               int step, int lds_cap, double sqrt_d) {
-    update_block<D, ATTN_SUM, G, NT>(L, C, N, a, src_kv, relayout, dense_seg_bytes, dense_cap,
-                                     recent_len, rs_num, rs_den, u, step, lds_cap, sqrt_d,
-                                     (int)blockIdx.x);
+                                               int step, int lds_cap, double sqrt_d, int group) {
+    update_block<D, SCORES, NT>(L, C, N, a, src_kv, relayout, dense_seg_bytes, dense_cap,
+                                recent_len, rs_num, rs_den, u, step, lds_cap, sqrt_d, group,
+                                (int)blockIdx.x);
 }
 
 // A step's append, periodic update and attention in one launch, for layers
@@ -990,8 +1074,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_u
         asm("" : "+v"(lane0));
         h = __builtin_amdgcn_readfirstlane(order[(int)blockIdx.x + lane0]);
     }
-    const int n = update_block<D, false, 1, T, true>(M, C, N, a, nullptr, 0, 0, 0, recent_len,
-                                               rs_num, rs_den, u, step, lds_cap, sqrt_d, h);
+    const int n = update_block<D, kScoresMeanLogit, T, true>(
+        M, C, N, a, nullptr, 0, 0, 0, recent_len, rs_num, rs_den, u, step, lds_cap, sqrt_d, 1, h);
     __syncthreads();  // the rows the update moved are read by other threads
     const AppendArgs none{};
     attn_block<D, false, T, false, TPR>(M, C, none, q, out, nullptr, 0, 0, pad_len, qscale, h,
@@ -1082,12 +1166,28 @@ int launch_budgets(const LayerDev& L, const Shape& s, const uint8_t* is_local,
     return last_error();
 }
 
-// Queries per group of the attention-sum scores: kQueryGroup when the period
-// has that many and their weights fit in the LDS, else 1.
-int update_query_group(int N, int cap, int d, int C, bool attn_scores, int period) {
-    if (!attn_scores || period < kQueryGroup) return 1;
-    return UpdateLds::bytes(N, cap, d, C, true, kQueryGroup, period) <= kUpdateLdsBudget ? kQueryGroup : 1;
+namespace {
+
+// Queries per group of the attention-sum scores: the window in the fewest
+// groups of at most kQueryGroup that fit the LDS, of equal size, when there is
+// room for kMinQueryGroup and the period has as many; else 1.  With more heads
+// than CUs, half of the LDS if that suffices: one block's in-order sums run
+// beside another's products.
+int update_query_group(const Shape& s, int cap, int period) {
+    if (period < kMinQueryGroup) return 1;
+    auto fits = [&](size_t budget) {
+        int g = kQueryGroup;
+        while (g > 1 && UpdateLds::bytes(s.N, cap, s.d, s.C, true, g, period) > budget) --g;
+        return g;
+    };
+    int g = s.BH > kCus ? fits(kUpdateLdsBudget / 2) : 1;
+    if (g < kMinQueryGroup) g = fits(kUpdateLdsBudget);
+    if (g < kMinQueryGroup) return 1;
+    const int groups = (period + g - 1) / g;
+    return (period + groups - 1) / groups;
 }
+
+}  // namespace
 
 int launch_update(const LayerDev& L, const Shape& s, const AppendArgs& a, const char* src_kv,
                   int relayout, int64_t dense_seg_bytes, int dense_cap, int recent_len,
@@ -1096,19 +1196,19 @@ int launch_update(const LayerDev& L, const Shape& s, const AppendArgs& a, const 
     hipStream_t st = (hipStream_t)stream;
     hipEvent_t e0 = static_cast<hipEvent_t>(ev_start), e1 = static_cast<hipEvent_t>(ev_stop);
     const bool attn = L.attn_scores != 0;
-    const int G = update_query_group(s.N, lds_cap, s.d, s.C, attn, L.ring_len);
-    const size_t lds = UpdateLds::bytes(s.N, lds_cap, s.d, s.C, attn, G, L.ring_len);
+    const int group = attn ? update_query_group(s, lds_cap, L.ring_len) : 1;
+    const size_t lds = UpdateLds::bytes(s.N, lds_cap, s.d, s.C, attn, group, L.ring_len);
     // allow the update block more than 64 KB of dynamic LDS (gfx950: 160 KB)
     static const bool lds_ok = [] {
         const int max_lds = 160 * 1024;
-        const void* fns[8] = {reinterpret_cast<const void*>(&k_update<128, false, 1, kBlock>),
-                              reinterpret_cast<const void*>(&k_update<128, false, 1, 1024>),
-                              reinterpret_cast<const void*>(&k_update<128, true, 1, kBlock>),
-                              reinterpret_cast<const void*>(&k_update<128, true, kQueryGroup, kBlock>),
-                              reinterpret_cast<const void*>(&k_update<64, false, 1, kBlock>),
-                              reinterpret_cast<const void*>(&k_update<64, false, 1, 1024>),
-                              reinterpret_cast<const void*>(&k_update<64, true, 1, kBlock>),
-                              reinterpret_cast<const void*>(&k_update<64, true, kQueryGroup, kBlock>)};
+#define HEADKV_UPDATE_FNS(D_)                                                  \
+    reinterpret_cast<const void*>(&k_update<D_, kScoresMeanLogit, kBlock>),    \
+        reinterpret_cast<const void*>(&k_update<D_, kScoresMeanLogit, 1024>),  \
+        reinterpret_cast<const void*>(&k_update<D_, kScoresAttnSingle, kBlock>), \
+        reinterpret_cast<const void*>(&k_update<D_, kScoresAttnGroup, kBlock>), \
+        reinterpret_cast<const void*>(&k_update<D_, kScoresAttnGroup, 512>)
+        const void* fns[] = {HEADKV_UPDATE_FNS(128), HEADKV_UPDATE_FNS(64)};
+#undef HEADKV_UPDATE_FNS
         bool ok = true;
         for (const void* f : fns)
             ok = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds) ==
@@ -1117,24 +1217,24 @@ int launch_update(const LayerDev& L, const Shape& s, const AppendArgs& a, const 
         return ok;
     }();
     (void)lds_ok;
-    // a CU per head: the whole CU's threads on it (the attention-sum variant
-    // keeps 256)
-    const bool wide = !attn && s.BH <= kCus;
-#define HEADKV_UPDATE(D_, A_, G_, NT_)                                                             \
-    hipExtLaunchKernelGGL((k_update<D_, A_, G_, NT_>), dim3(s.BH), dim3(NT_), lds, st, e0, e1, 0,  \
-                          L, s.C, s.N, a, src_kv, relayout, dense_seg_bytes, dense_cap,           \
-                          recent_len, rs_num, rs_den, u, step, lds_cap, sqrt_d)
+    // a CU per head: the whole CU's threads on it
+    const bool wide = s.BH <= kCus;
+#define HEADKV_UPDATE(D_, S_, NT_)                                                                 \
+    hipExtLaunchKernelGGL((k_update<D_, S_, NT_>), dim3(s.BH), dim3(NT_), lds, st, e0, e1, 0, L,  \
+                          s.C, s.N, a, src_kv, relayout, dense_seg_bytes, dense_cap, recent_len,  \
+                          rs_num, rs_den, u, step, lds_cap, sqrt_d, group)
+#define HEADKV_UPDATE_D(D_)                                                  \
+    if (!attn && wide) HEADKV_UPDATE(D_, kScoresMeanLogit, 1024);            \
+    else if (!attn) HEADKV_UPDATE(D_, kScoresMeanLogit, kBlock);             \
+    else if (group == 1) HEADKV_UPDATE(D_, kScoresAttnSingle, kBlock);       \
+    else if (wide) HEADKV_UPDATE(D_, kScoresAttnGroup, 512);                 \
+    else HEADKV_UPDATE(D_, kScoresAttnGroup, kBlock)
     if (s.d == 128) {
-        if (wide) HEADKV_UPDATE(128, false, 1, 1024);
-        else if (!attn) HEADKV_UPDATE(128, false, 1, kBlock);
-        else if (G == kQueryGroup) HEADKV_UPDATE(128, true, kQueryGroup, kBlock);
-        else HEADKV_UPDATE(128, true, 1, kBlock);
+        HEADKV_UPDATE_D(128);
     } else {
-        if (wide) HEADKV_UPDATE(64, false, 1, 1024);
-        else if (!attn) HEADKV_UPDATE(64, false, 1, kBlock);
-        else if (G == kQueryGroup) HEADKV_UPDATE(64, true, kQueryGroup, kBlock);
-        else HEADKV_UPDATE(64, true, 1, kBlock);
+        HEADKV_UPDATE_D(64);
     }
+#undef HEADKV_UPDATE_D
 #undef HEADKV_UPDATE
     return last_error();
 }
