@@ -213,9 +213,13 @@ __global__ __launch_bounds__(kBlock) void k_score(LayerDev L, const uint16_t* q,
 // ------------------------------------------------------------------ budgets
 // With cfg_pairs, batch rows 2i (conditional) and 2i+1 (unconditional) form a
 // guidance pair and both take the labels of row 2i.
+// host: pinned host memory, budgets then labels [BH] each, which the host reads
+// once the kernel has ended: two device-to-host copies of a few hundred bytes
+// took as long as the grouping kernel.
 __global__ void k_budgets(LayerDev L, int H, int N, const uint8_t* is_local,
                           const int32_t* override_b, int32_t* budgets, int mode, int row_len,
-                          int recent_len, int rho_num, int rho_den, int cfg_pairs) {
+                          int recent_len, int rho_num, int rho_den, int cfg_pairs,
+                          int32_t* host) {
     __shared__ int n_local;
     const int b = blockIdx.x, h = threadIdx.x, idx = b * H + h;
     if (h == 0) n_local = 0;
@@ -242,6 +246,21 @@ __global__ void k_budgets(LayerDev L, int H, int N, const uint8_t* is_local,
     budgets[idx] = B;
     L.budget[idx] = B;
     L.label[idx] = loc;
+    host[idx] = B;
+    host[(int)(gridDim.x * blockDim.x) + idx] = loc;
+}
+
+// The tables of the new layout from pinned host memory into the metadata, in
+// one launch (five copies before, each longer than this).
+__global__ __launch_bounds__(kBlock) void k_tables(LayerDev L, LayoutTables t, int BH) {
+    const int i = (int)(blockIdx.x * kBlock + threadIdx.x);
+    if (i < BH) {
+        L.seg_off[i] = t.seg_off[i];
+        L.cap[i] = t.cap[i];
+        L.order[i] = t.order[i];
+    }
+    if (i <= BH) L.item_start[i] = t.item_start[i];
+    if (i < t.n_items) L.items[i] = t.items[i];
 }
 
 // ------------------------------------------------------------------- update
@@ -1159,10 +1178,18 @@ int launch_score(const LayerDev& L, const Shape& s, const uint16_t* q, int32_t* 
 
 int launch_budgets(const LayerDev& L, const Shape& s, const uint8_t* is_local,
                    const int32_t* override_b, int32_t* budgets, int mode, int row_len,
-                   int recent_len, int rho_num, int rho_den, int cfg_pairs, void* stream) {
+                   int recent_len, int rho_num, int rho_den, int cfg_pairs, int32_t* host,
+                   void* stream) {
     hipLaunchKernelGGL(k_budgets, dim3(s.B), dim3(s.H), 0, (hipStream_t)stream, L, s.H, s.N,
                        is_local, override_b, budgets, mode, row_len, recent_len, rho_num, rho_den,
-                       cfg_pairs);
+                       cfg_pairs, host);
+    return last_error();
+}
+
+int launch_tables(const LayerDev& L, const Shape& s, const LayoutTables& t, void* stream) {
+    const int n = t.n_items > s.BH + 1 ? t.n_items : s.BH + 1;
+    hipLaunchKernelGGL(k_tables, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0,
+                       (hipStream_t)stream, L, t, s.BH);
     return last_error();
 }
 

@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -215,6 +216,69 @@ LayerDev dev_of(headkv_t h, const Layer& L) {
     D.dn = L.dn;
     return D;
 }
+
+// Pinned host memory through which headkv_assign_budgets and its kernels
+// exchange budgets and tables.  A call takes a buffer and gives it back when the
+// stream has been waited for, so none is in use by the GPU outside a call.
+// Buffers that are not in use are kept for the next call (pinning one takes
+// longer than the call): at most kKept of them, of at most kKeptBytes each.
+class Stage {
+  public:
+    Stage() = default;
+    Stage(const Stage&) = delete;
+    Stage& operator=(const Stage&) = delete;
+    ~Stage() {
+        if (!p_) return;
+        if (bytes_ <= kKeptBytes) {
+            std::lock_guard<std::mutex> lock(pool().mutex);
+            if (pool().n < kKept) {
+                pool().kept[pool().n++] = {p_, bytes_};
+                return;
+            }
+        }
+        (void)hipHostFree(p_);
+    }
+    int take(size_t bytes) {
+        {
+            std::lock_guard<std::mutex> lock(pool().mutex);
+            for (int i = 0; i < pool().n; ++i) {
+                if (pool().kept[i].bytes < bytes) continue;
+                p_ = pool().kept[i].p;
+                bytes_ = pool().kept[i].bytes;
+                pool().kept[i] = pool().kept[--pool().n];
+                return 0;
+            }
+        }
+        bytes_ = align_up(bytes, 1 << 16);
+        // allowed while another thread captures a graph
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        const hipError_t e = hipHostMalloc(&p_, bytes_, hipHostMallocPortable | hipHostMallocCoherent);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e != hipSuccess) p_ = nullptr;
+        return (int)e;
+    }
+    char* data() const { return static_cast<char*>(p_); }
+
+  private:
+    static constexpr int kKept = 4;
+    static constexpr size_t kKeptBytes = 1 << 20;
+    struct Buffer {
+        void* p;
+        size_t bytes;
+    };
+    struct Pool {
+        std::mutex mutex;
+        Buffer kept[kKept];
+        int n = 0;
+    };
+    static Pool& pool() {
+        static Pool& p = *new Pool;  // outlives every handle
+        return p;
+    }
+    void* p_ = nullptr;
+    size_t bytes_ = 0;
+};
 
 // Event pair for a sampled launch of `kind`, or nullptrs.
 void take_events(headkv_t h, bool time_it, int kind, double bytes, void** e0, void** e1) {
@@ -766,27 +830,29 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
     const int BH = h->shape.BH;
     hipStream_t s = (hipStream_t)stream;
     LayerDev Dold = dev_of(h, L);
+    // budgets and labels [BH] int32 each; then the tables: offsets [BH] int64,
+    // capacities and order [BH], first entries [BH + 1], entries
+    const size_t tables_at = align_up(2 * sizeof(int32_t) * BH, 256);
+    Stage stage;
+    st = hip_status(stage.take(tables_at + sizeof(int64_t) * BH + sizeof(int32_t) * (3 * (size_t)BH + 1) +
+                               sizeof(uint32_t) * (size_t)h->ml.max_items),
+                    "staging memory");
+    if (st) return st;
+    int32_t* bud = reinterpret_cast<int32_t*>(stage.data());
+    const int32_t* lab = bud + BH;  // the labels the budgets used (cfg pairs applied)
     st = hip_status(launch_budgets(Dold, h->shape, is_local, budget_override, budgets, c.budget_mode,
-                                   c.row_len, c.recent_len, c.rho_num, c.rho_den, c.cfg_pairs, stream),
+                                   c.row_len, c.recent_len, c.rho_num, c.rho_den, c.cfg_pairs, bud,
+                                   stream),
                     "budget launch");
-    if (st) return st;
-    std::vector<int32_t> bud(BH);
-    std::vector<int32_t> lab(BH);  // the labels the budgets used (cfg pairs applied)
-    st = hip_status(hipMemcpyAsync(bud.data(), budgets, sizeof(int32_t) * BH, hipMemcpyDeviceToHost, s),
-                    "budget read-back");
-    if (!st) st = hip_status(hipMemcpyAsync(lab.data(), Dold.label, sizeof(int32_t) * BH,
-                                            hipMemcpyDeviceToHost, s),
-                             "label read-back");
-    if (st) {
-        (void)hipStreamSynchronize(s);
-        return st;
-    }
-    st = hip_status(hipStreamSynchronize(s), "stream wait");
-    if (st) return st;
+    headkv_status st_sync = hip_status(hipStreamSynchronize(s), "stream wait");
+    if (st || st_sync) return st ? st : st_sync;
     // segments: prefix + min(budget + P, N) slots each, in head order
-    std::vector<int64_t> off(BH);
-    std::vector<int32_t> cap(BH);
-    std::vector<int> cap_i(BH);
+    int64_t* off = reinterpret_cast<int64_t*>(stage.data() + tables_at);
+    int32_t* cap_t = reinterpret_cast<int32_t*>(off + BH);
+    int32_t* order = cap_t + BH;
+    int32_t* item_start = order + BH;
+    uint32_t* items = reinterpret_cast<uint32_t*>(item_start + BH + 1);
+    std::vector<int> cap(BH);
     size_t total = 0;
     for (int i = 0; i < BH; ++i) {
         if (bud[i] < 1 || bud[i] > c.num_visual)
@@ -796,11 +862,11 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
             return fail(HEADKV_ERR_UNSUPPORTED, "budget + period exceeds HEADKV_MAX_CAPACITY");
     }
     if (c.attn_strategy == HEADKV_ATTN_PADDED) {  // every head padded to the largest
-        const int32_t cmax = *std::max_element(cap.begin(), cap.end());
+        const int cmax = *std::max_element(cap.begin(), cap.end());
         std::fill(cap.begin(), cap.end(), cmax);
     }
     for (int i = 0; i < BH; ++i) {
-        cap_i[i] = cap[i];
+        cap_t[i] = cap[i];
         off[i] = (int64_t)total;
         total += segment_bytes(c.prefix_len, cap[i], c.head_dim);
     }
@@ -810,38 +876,33 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
     // attention dispatch order: longest heads first, so that when a layer
     // needs more than one round of blocks the short heads fill the tail; with
     // HEADKV_ATTN_GROUPED the global heads, then the local heads
-    std::vector<int32_t> order(BH);
     for (int i = 0; i < BH; ++i) order[i] = i;
     if (c.attn_strategy == HEADKV_ATTN_GROUPED)
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return lab[a] < lab[b]; });
+        std::stable_sort(order, order + BH, [&](int a, int b) { return lab[a] < lab[b]; });
     else
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cap[a] > cap[b]; });
+        std::stable_sort(order, order + BH, [&](int a, int b) { return cap[a] > cap[b]; });
     int n_global = 0;
     for (int i = 0; i < BH; ++i) n_global += lab[i] ? 0 : 1;
     // chunk table of the new layout, the chunks of a head contiguous
-    const int chunk_threads = pick_chunk_threads(c.prefix_len, c.head_dim, cap_i);
-    std::vector<uint32_t> items;
-    std::vector<int32_t> item_start(BH + 1);
+    const int chunk_threads = pick_chunk_threads(c.prefix_len, c.head_dim, cap);
+    int n_items = 0;
     for (int i = 0; i < BH; ++i) {
-        item_start[i] = (int32_t)items.size();
+        item_start[i] = n_items;
         const int nc = chunks_of(c.prefix_len, cap[i], chunk_threads, c.head_dim);
-        for (int k = 0; k < nc; ++k) items.push_back(((uint32_t)i << 8) | (uint32_t)k);
+        for (int k = 0; k < nc; ++k) items[n_items++] = ((uint32_t)i << 8) | (uint32_t)k;
     }
-    item_start[BH] = (int32_t)items.size();
-    // tables of the new layout (the host vectors outlive the copies: the stream
-    // is waited for below on every path)
-    char* mb = static_cast<char*>(L.meta);
-    st = hip_status(hipMemcpyAsync(mb + h->ml.seg_off, off.data(), sizeof(int64_t) * BH, hipMemcpyHostToDevice, s), "table upload");
-    if (!st) st = hip_status(hipMemcpyAsync(mb + h->ml.cap, cap.data(), sizeof(int32_t) * BH, hipMemcpyHostToDevice, s), "table upload");
-    if (!st) st = hip_status(hipMemcpyAsync(mb + h->ml.order, order.data(), sizeof(int32_t) * BH, hipMemcpyHostToDevice, s), "table upload");
-    if (!st) st = hip_status(hipMemcpyAsync(mb + h->ml.items, items.data(), sizeof(uint32_t) * items.size(), hipMemcpyHostToDevice, s), "table upload");
-    if (!st) st = hip_status(hipMemcpyAsync(mb + h->ml.item_start, item_start.data(), sizeof(int32_t) * (BH + 1), hipMemcpyHostToDevice, s), "table upload");
+    item_start[BH] = n_items;
+    // tables of the new layout (the staging memory outlives the launch: the
+    // stream is waited for below on every path)
+    LayerDev Dnew = make_layer_dev(ragged_kv, L.meta, h->ml);
+    st = hip_status(launch_tables(Dnew, h->shape,
+                                  LayoutTables{off, cap_t, order, item_start, items, n_items}, stream),
+                    "table upload");
     // padded rows are read (and masked) by the attention: keep them finite
     if (!st && c.attn_strategy == HEADKV_ATTN_PADDED)
         st = hip_status(hipMemsetAsync(ragged_kv, 0, total, s), "ragged clear");
     // first update, fused with the move from the dense buffer into the segments
     if (!st) {
-        LayerDev Dnew = make_layer_dev(ragged_kv, L.meta, h->ml);
         Dnew.dn = L.dn;  // the lengths it moves: prefill's 0 plus every append since
         AppendArgs none{};
         st = hip_status(launch_update(Dnew, h->shape, none, static_cast<const char*>(L.dense), 1,
@@ -859,11 +920,11 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
     }
     L.ragged = ragged_kv;
     L.grouped = true;
-    L.budget.assign(bud.begin(), bud.end());
-    L.label_local.assign(lab.begin(), lab.end());
+    L.budget.assign(bud, bud + BH);
+    L.label_local.assign(lab, lab + BH);
     L.cap.assign(cap.begin(), cap.end());
     L.chunk_threads = chunk_threads;
-    L.items = (int)items.size();
+    L.items = n_items;
     L.n_global = n_global;
     for (int i = 0; i < BH; ++i) L.n[i] = std::min(L.n[i], L.budget[i]);
     L.dn = 0;  // the relayout wrote every head's length

@@ -145,10 +145,20 @@ int launch_prefill_attn(const LayerDev& L, const Shape& s, const uint16_t* qc, c
 int launch_score(const LayerDev& L, const Shape& s, const uint16_t* q, int32_t* n_star,
                  uint8_t* is_local, int len, double sqrt_d, double tau, int local_window,
                  void* stream);
-// Writes budgets and the labels the updates use (L.label) for every head.
+// Writes budgets and the labels the updates use (L.label) for every head, and
+// both into host (pinned, [2][BH]).
 int launch_budgets(const LayerDev& L, const Shape& s, const uint8_t* is_local,
                    const int32_t* override_b, int32_t* budgets, int mode, int row_len,
-                   int recent_len, int rho_num, int rho_den, int cfg_pairs, void* stream);
+                   int recent_len, int rho_num, int rho_den, int cfg_pairs, int32_t* host,
+                   void* stream);
+// The metadata tables of a layer's per-head segments, in pinned host memory.
+struct LayoutTables {
+    const int64_t* seg_off;
+    const int32_t *cap, *order, *item_start;
+    const uint32_t* items;
+    int n_items;
+};
+int launch_tables(const LayerDev& L, const Shape& s, const LayoutTables& t, void* stream);
 // a.k == nullptr: no append.  step: the visual step of the update.
 // lds_cap: largest visual capacity among the launch's source segments.
 // With L.attn_scores, global heads are scored by the window's attention weights.
