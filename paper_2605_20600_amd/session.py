@@ -62,7 +62,9 @@ class Session:
 
     @staticmethod
     def stream() -> int:
-        return torch.cuda.current_stream().cuda_stream
+        # torch.cuda.current_stream().cuda_stream without its Stream object: 0.2
+        # us instead of 2.9, of the 5 us that a small launch takes
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
     def close(self):
         if self.h:
