@@ -91,11 +91,19 @@ __device__ __forceinline__ int swizzle(int row) {
 // for the next tile's loads in front of this tile's reads; the caller waits
 // (lds_loads_done) before the barrier after which the tile is read.  Nothing
 // else here uses m0 (LDS instructions of gfx950 do not).
+// ONCE: the rows are read by no other block (non-temporal).
+template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds(const uint16_t* src, uint32_t dst) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :
-                 : "v"(src), "s"(dst)
-                 : "memory");
+    if constexpr (ONCE)
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
+                     :
+                     : "v"(src), "s"(dst)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                     :
+                     : "v"(src), "s"(dst)
+                     : "memory");
 }
 __device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

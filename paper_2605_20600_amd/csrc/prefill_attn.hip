@@ -25,20 +25,22 @@
 // launch stores the prefix keys and values into the cache (headkv_prefill):
 // each block writes the rows of its own queries from the tiles in LDS.
 //
-// Long prefixes are bound by the two MFMA chains of a wavefront and the
-// softmax between them (C = 2048, 64 heads of 128: 29 % of the matrix cores'
-// cycles, no LDS bank conflicts), short ones by the loads, then the stores, of
-// blocks that all run at once.  Per launch, with the tiles staged through
-// registers, V read four 2-byte elements at a time and 32x32x8 steps, and now:
-// C = 2048, 64 heads of 128 492 -> 102 us (674 TFLOP/s of causal products);
-// C = 300, 320 heads of 64 38.8 -> 21.7 us; C = 128, 256 heads of 128 18.4 ->
-// 15.3 us; C = 64, 512 heads of 128 20.3 -> 15.0 us (3.9 TB/s).
+// Long prefixes are bound inside the CU (C = 2048, 64 heads of 128: 29 % of the
+// matrix cores' cycles, 44 % of the vector ALU's issue, no LDS bank conflicts;
+// without the loads of the tiles it would take 24 % less, without the
+// exponentials 6 %), short ones by their bytes.  Per launch, with the tiles
+// staged through registers, V read four 2-byte elements at a time, 32x32x8
+// steps and everything written through the L2, and now: C = 2048, 64 heads of
+// 128 492 -> 100 us (690 TFLOP/s of causal products); C = 300, 320 heads of 64
+// 38.8 -> 18.0 us; C = 128, 256 heads of 128 18.4 -> 11.5 us; C = 64, 512 heads
+// of 128 20.3 -> 10.7 us (5.5 TB/s).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "../../include/headkv.h"
 #include "device_common.h"
@@ -53,6 +55,18 @@ typedef short bf16x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+
+// What the kernel writes leaves as whole rows, past the L2 (non-temporal):
+// written back from the L2 it takes longer than the reads (8 launches, C = 128,
+// 256 heads of 128: 122 us through the L2, 108 with the cache rows past it, 92
+// with the output too; 18.2 and 17.9 us for one launch and a conversion of its
+// output to bf16, 17.9 and 14.5 for one launch and a decode step).
+template <typename T>
+__device__ __forceinline__ void nt_store(const T& v, T* p) {
+    __builtin_nontemporal_store(v, p);
+}
 
 __device__ __forceinline__ bf16x8_t load8(const uint16_t* p) {
     const uint4 w = *reinterpret_cast<const uint4*>(p);
@@ -64,7 +78,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2)))
 void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
                     const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
                     float* __restrict__ out, int C, float qscale, int64_t seg_bytes,
-                    int dense_cap, int dense_chunks) {
+                    int dense_cap, int dense_chunks, int through_lds) {
     constexpr int KS = D / 16;           // 32x32x16 steps over d
     constexpr int MB = D / 32;           // 32-dim blocks of the output
     constexpr int CH = D / 8;            // 16-byte pieces of a row
@@ -90,21 +104,25 @@ void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
     // a piece's place in its load is the lane's; the lane fetches the piece
     // that belongs there.  Rows past C: row C - 1 again (finite, masked).
-    auto load_tile = [&](int kb, int buf) {
+    auto load_tile = [&](int kb, int buf, auto once) {
+        constexpr bool ONCE = decltype(once)::value;
 #pragma unroll
         for (int i0 = 0; i0 < NP; i0 += W) {
             const int i = i0 + wave;
             const int p = i * 64 + lane, row = p / CH, c = (p % CH) ^ swizzle<D>(row);
             const size_t src = (size_t)min(kb * KT + row, C - 1) * D + c * 8;
             const uint32_t dst = lds0 + (buf * 2 * KT) * ROWB + i * 1024;
-            load_to_lds(K + src, dst);
-            load_to_lds(V + src, dst + KT * ROWB);
+            load_to_lds<ONCE>(K + src, dst);
+            load_to_lds<ONCE>(V + src, dst + KT * ROWB);
         }
     };
     const int nk = (min(C, (tile + 1) * QT) + KT - 1) / KT;  // key tiles of this block
-    load_tile(0, 0);
+    if (tiles == 1 && nk == 1)  // no other block reads these rows (C = 64, 512 heads: -3 %)
+        load_tile(0, 0, std::true_type{});
+    else
+        load_tile(0, 0, std::false_type{});
     // up to two tiles: one round trip for both
-    if (nk == 2) load_tile(1, 1);
+    if (nk == 2) load_tile(1, 1, std::false_type{});
     bf16x8_t qb[KS];
 #pragma unroll
     for (int s = 0; s < KS; ++s)
@@ -117,8 +135,8 @@ void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[mb][r] = 0.f;
     const SegPtrs cache = seg_ptrs(L.kv + (int64_t)bh * seg_bytes, C, dense_cap, D);
-    uint4* cK = reinterpret_cast<uint4*>(cache.K);
-    uint4* cV = reinterpret_cast<uint4*>(cache.V);
+    u32x4_t* cK = reinterpret_cast<u32x4_t*>(cache.K);
+    u32x4_t* cV = reinterpret_cast<u32x4_t*>(cache.V);
     // this lane's part of the operand addresses: K row j, piece 2 s + half;
     // V rows 4 half + (lane & 15) / 4 (and 8 on), dims 16 ((lane >> 4) & 1) +
     // 4 (lane & 3) of a 32-dim block
@@ -222,16 +240,17 @@ void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
         // every wavefront's, and all are done with the other buffer
         lds_loads_done();
         __syncthreads();
-        if (nk > 2 && kb + 1 < nk) load_tile(kb + 1, buf ^ 1);
+        if (nk > 2 && kb + 1 < nk) load_tile(kb + 1, buf ^ 1, std::false_type{});
         if ((kb + 1) * KT > tile * QT) {  // rows of this block's queries: into the cache
 #pragma unroll
             for (int i0 = 0; i0 < NP; i0 += W) {
                 const int p = (i0 + wave) * 64 + lane, row = p / CH;
                 const int c = (p % CH) ^ swizzle<D>(row), key = kb * KT + row;
-                const uint4* src = reinterpret_cast<const uint4*>(lds + (buf * 2 * KT) * ROWB) + p;
+                const u32x4_t* src =
+                    reinterpret_cast<const u32x4_t*>(lds + (buf * 2 * KT) * ROWB) + p;
                 if (key < C) {
-                    cK[(size_t)key * CH + c] = src[0];
-                    cV[(size_t)key * CH + c] = src[KT * CH];
+                    nt_store(src[0], cK + (size_t)key * CH + c);
+                    nt_store(src[KT * CH], cV + (size_t)key * CH + c);
                 }
             }
         }
@@ -251,22 +270,15 @@ void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
     // accumulator r of block mb: dim 32 mb + 8 (r / 4) + 4 half + r % 4, i.e.
     // piece 8 mb + 2 (r / 4) + half of the row's 16-byte pieces
     auto piece = [&](int mb, int g) {
-        float4 v;
-        v.x = acc[mb][4 * g] * inv;
-        v.y = acc[mb][4 * g + 1] * inv;
-        v.z = acc[mb][4 * g + 2] * inv;
-        v.w = acc[mb][4 * g + 3] * inv;
-        return v;
+        return f32x4_t{acc[mb][4 * g] * inv, acc[mb][4 * g + 1] * inv, acc[mb][4 * g + 2] * inv,
+                       acc[mb][4 * g + 3] * inv};
     };
     constexpr int OP = D / 4;  // pieces of an output row
-    float4* o = reinterpret_cast<float4*>(out + base + (size_t)q0 * D);
-    if constexpr (D == 64) {
-        // through LDS (this wavefront's 32 rows, the pieces permuted within
-        // the row), so that whole rows leave together: C = 300, 320 heads 22.5
-        // -> 21.7 us.  At d = 128, where a row is 512 bytes, writing from the
-        // accumulators is 2 % faster (C = 64 and 128, 512 and 256 heads).
+    f32x4_t* o = reinterpret_cast<f32x4_t*>(out + base + (size_t)q0 * D);
+    if (through_lds) {
+        // this wavefront's 32 rows, the pieces permuted within the row
         __syncthreads();  // every wavefront is done with the tiles
-        float4* ob = reinterpret_cast<float4*>(lds) + wave * 32 * OP;
+        f32x4_t* ob = reinterpret_cast<f32x4_t*>(lds) + wave * 32 * OP;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -275,8 +287,8 @@ void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
 #pragma unroll
         for (int i = 0; i < OP / 2; ++i) {
             const int row = (i * 64 + lane) / OP, c = lane & (OP - 1);
-            const float4 v = ob[row * OP + (c ^ (row & (OP - 1)))];
-            if (q0 + row < C) o[row * OP + c] = v;
+            const f32x4_t v = ob[row * OP + (c ^ (row & (OP - 1)))];
+            if (q0 + row < C) nt_store(v, o + row * OP + c);
         }
     } else if (q0 + j < C) {
 #pragma unroll
@@ -305,25 +317,34 @@ void prefill_attn_launch(const PrefillCall& c) {
     const float qscale = (float)(1.4426950408889634 / std::sqrt((double)D));
     const unsigned grid = (unsigned)((c.s.C + QT - 1) / QT) * (unsigned)c.s.BH;
     const size_t tile_bytes = (size_t)2 * KT * D * sizeof(uint16_t);
-    const size_t out_bytes = D == 64 ? (size_t)32 * W * D * sizeof(float) : 0;
+    // The output rows go through LDS to leave whole (and non-temporally: half
+    // a row at a time that would be slower than through the L2, C = 128, 256
+    // heads of 128: 192 us for 8 launches, 122 through the L2, 92 as whole
+    // rows) unless the launch is so small that its latency counts: 32 heads of
+    // 128, C = 200: 9.3 us, as whole rows 10.2; C = 300: 11.3 and 11.1; 256
+    // heads, C = 64: 7.6 and 6.5.  At d = 64 whole rows are never slower.
+    const int through_lds = D == 64 || (long long)c.s.BH * c.s.C >= 8192;
+    const size_t out_bytes = through_lds ? (size_t)32 * W * D * sizeof(float) : 0;
     const size_t lds = std::max(tile_bytes * (c.s.C > KT ? 2 : 1), out_bytes);
     hipExtLaunchKernelGGL((k_prefill_attn<D, W, SUBS>), dim3(grid), dim3(64 * W), lds, c.st,
                           c.e0, c.e1, 0, c.L, c.s.BH, c.qc, c.kc, c.vc, c.out, c.s.C, qscale,
-                          c.dense_seg_bytes, c.dense_cap, c.dense_chunks);
+                          c.dense_seg_bytes, c.dense_cap, c.dense_chunks, through_lds);
 }
 
 // Wavefronts (of 32 queries) per block.  Four: the keys in LDS serve 128
 // queries (C = 300, 256 heads of 128: 29.9 us, with two 35.3, with one 61.0; C
 // = 2048, 64 heads: 103, 141 and 297).  Up to 128 tokens a head is one such
-// block, and with at most one head per CU half of it finds room beside each
-// other: two, twice as many blocks (C = 77 / 128, 256 heads: 10.2 / 12.6 ->
-// 9.2 / 12.2 us; with 512 heads two would be slower, 20.0 -> 25.4 us).  Up to
-// 64 (32) tokens two (one) hold all queries.
+// block; two make two blocks of it, which is better as long as all of them are
+// resident at once, two to a CU at d = 128, four at 64 (C = 77 / 128, d = 128,
+// with four and with two: 256 heads 8.3 / 9.9 and 7.5 / 9.7 us, 320 heads 10.7
+// / 12.9 and 13.0 / 15.7; d = 64, 512 heads 7.6 / 8.5 and 6.9 / 8.3, 1024 heads
+// 10.9 / 19.9 and 12.7 / 19.4).  Up to 64 (32) tokens two (one) hold all
+// queries.
 template <int D>
 void prefill_attn_dispatch(const PrefillCall& c) {
     const int C = c.s.C;
     if (C <= 32) prefill_attn_launch<D, 1, 1>(c);
-    else if (C <= 64 || (C <= 128 && c.s.BH <= kCus)) prefill_attn_launch<D, 2, 2>(c);
+    else if (C <= 64 || (C <= 128 && c.s.BH <= kCus * 128 / D)) prefill_attn_launch<D, 2, 2>(c);
     else prefill_attn_launch<D, 4, 2>(c);
 }
 

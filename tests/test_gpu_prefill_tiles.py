@@ -1,6 +1,7 @@
 """Prefix prefill attention at the edges of its tiles: 32-query wavefronts, key
-tiles of 32 and 64, blocks of one, two and four wavefronts (the last two also
-depend on the number of heads), ragged last tiles, against fp64 torch on the
+tiles of 32 and 64, blocks of one, two and four wavefronts (the last two, and
+how the output is written, also depend on the number of heads), ragged last
+tiles, against fp64 torch on the
 same inputs; and the prefix rows it stores, through the attention of the first
 decode step."""
 import math
@@ -25,7 +26,7 @@ def _causal(q, k, v):
 @pytest.mark.parametrize("C,batch,heads", [
     (2, 1, 3), (31, 2, 4), (32, 1, 5), (33, 1, 5), (63, 1, 3), (64, 3, 4), (65, 1, 3),
     (96, 1, 3), (127, 1, 8), (128, 1, 3), (129, 1, 3), (192, 1, 2), (257, 1, 3),
-    (100, 8, 32), (100, 257, 1), (128, 9, 32)])
+    (100, 8, 32), (100, 257, 1), (128, 9, 32), (70, 513, 1)])
 def test_prefill_tiles(C, batch, heads, d):
     wl = W.LUMINA768.with_(batch=batch, heads=heads, layers=1, head_dim=d, prefix_len=C,
                            grid_rows=2, grid_cols=4, period=5, group_threshold=5,
