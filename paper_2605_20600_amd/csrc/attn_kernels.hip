@@ -99,7 +99,10 @@ template <int D, int T>
 void attn_dispatch_t(const LayerDev& L, const Shape& s, const AppendArgs& a, const uint16_t* q,
                      float* out, uint64_t* partials, const AttnPlan& p, hipStream_t st,
                      hipEvent_t ev0, hipEvent_t ev1) {
-    if (p.chunked)
+    if (p.chunked && T == kAttnMaxThreads && p.tpr == kAttnTprWide)
+        attn_launch<D, kAttnMaxThreads, true, kAttnTprWide>(L, s, a, q, out, partials, p, st, ev0,
+                                                            ev1);
+    else if (p.chunked)
         attn_launch<D, T, true, kAttnTpr>(L, s, a, q, out, partials, p, st, ev0, ev1);
     else if (p.tpr == kAttnTpr)
         attn_launch<D, T, false, kAttnTpr>(L, s, a, q, out, partials, p, st, ev0, ev1);

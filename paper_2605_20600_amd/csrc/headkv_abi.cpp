@@ -48,6 +48,7 @@ struct Layer {
     int dn = 0;
     std::vector<uint8_t> label_local;  // labels used by the updates (host copy)
     int chunk_threads = kAttnMaxThreads;  // block size the chunk table is cut for
+    int chunk_tpr = kAttnTpr;             // and tokens per row of its one pass
     int items = 0;                        // entries of the chunk table
     int n_global = 0;                     // global heads (first in the dispatch
                                           // order with HEADKV_ATTN_GROUPED)
@@ -137,8 +138,8 @@ struct Plan {
 
 // Chunks of one pass of a `threads`-thread block that cover a head of
 // capacity `cap` (prefix, slots and the token being appended).
-int chunks_of(int C, int cap, int threads, int d) {
-    const int tp = attn_tokens_per_pass(threads, d);
+int chunks_of(int C, int cap, int threads, int d, int tpr = kAttnTpr) {
+    const int tp = attn_tokens_per_pass(threads, d, tpr);
     return (C + cap + 1 + tp - 1) / tp;
 }
 
@@ -161,29 +162,43 @@ Plan make_plan(const headkv_config& c) {
     return p;
 }
 
+// Block size (and tokens per row) of a chunk table.
+struct ChunkPass {
+    int threads, tpr;
+};
+
 // Block size of a chunk table for the given capacities: the smallest whose
 // chunks are at most one per CU (the launch then waits for one short pass on
 // as many CUs as there are chunks, and the merge of a head's extra chunks
 // costs less than the longer pass: 32 heads of 250-450 tokens, d = 128, 256 /
 // 512 / 1024 threads 5.21 / 5.61 / 6.92 us per launch; 128 such heads, 7.73 /
 // 7.11 / 7.69, the 512-thread table is the smallest that fits; 4 heads 4.79 /
-// 5.22 / 6.25).  With more chunks than CUs at every size, the fewest rounds of
-// resident blocks, then the largest blocks (192 heads of up to 765 tokens, 512
-// / 1024 threads in one / two rounds: 11.8 / 15.7 us).
-int pick_chunk_threads(int C, int d, const std::vector<int>& cap) {
+// 5.22 / 6.25).  With more chunks than CUs at every size, the largest block's
+// wide pass if its fewer chunks then fit (Lumina-1024: 128 heads of 1 to 16
+// rows, in most layers 230-250 chunks of 576 tokens, else 460 of 256: 10.92 ->
+// 10.68 us per launch over all layers, whole job +2.1 %); else the fewest
+// rounds of resident blocks, then the largest blocks (192 heads of up to 765
+// tokens, 512 / 1024 threads in one / two rounds: 11.8 / 15.7 us).
+ChunkPass pick_chunk_pass(int C, int d, const std::vector<int>& cap) {
+    auto count = [&](int t, int tpr) {
+        long long items = 0;
+        for (int x : cap) items += chunks_of(C, x, t, d, tpr);
+        return items;
+    };
+    for (int t = kAttnMinThreads; t <= kAttnMaxThreads; t *= 2)
+        if (count(t, kAttnTpr) <= kCus) return {t, kAttnTpr};
+    if (count(kAttnMaxThreads, kAttnTprWide) <= kCus) return {kAttnMaxThreads, kAttnTprWide};
     int best = kAttnMaxThreads;
     long long best_rounds = -1;
     for (int t = kAttnMaxThreads; t >= kAttnMinThreads; t /= 2) {
-        long long items = 0;
-        for (int x : cap) items += chunks_of(C, x, t, d);
         const long long slots = attn_resident_blocks(t);
-        const long long rounds = (items + slots - 1) / slots;
-        if (best_rounds < 0 || rounds < best_rounds || items <= kCus) {
+        const long long rounds = (count(t, kAttnTpr) + slots - 1) / slots;
+        if (best_rounds < 0 || rounds < best_rounds) {
             best = t;
             best_rounds = rounds;
         }
     }
-    return best;
+    return {best, kAttnTpr};
 }
 
 // Block size of the full-cache chunk table.  Before grouping every head grows
@@ -379,6 +394,7 @@ headkv_status prefill_impl(headkv_t h, int32_t layer, const uint16_t* q_c, const
     L.budget.assign(h->shape.BH, 0);
     L.label_local.assign(h->shape.BH, 0);
     L.chunk_threads = dense_chunk_threads(h->shape.BH, c.prefix_len, h->dense_cap, c.head_dim);
+    L.chunk_tpr = kAttnTpr;
     const int dense_chunks = chunks_of(c.prefix_len, h->dense_cap, L.chunk_threads, c.head_dim);
     L.items = h->shape.BH * dense_chunks;
     if (q_c) {
@@ -540,7 +556,7 @@ int attn_plans(headkv_t h, const Layer& L, bool appended, AttnPlan* out) {
         return k;
     }
     if (BH < kCus) {
-        out[0] = AttnPlan{L.chunk_threads, 1, L.items, BH, 0, 0, 0, kAttnTpr};
+        out[0] = AttnPlan{L.chunk_threads, 1, L.items, BH, 0, 0, 0, L.chunk_tpr};
         return 1;
     }
     // with more than one block per CU, longest heads first (after grouping;
@@ -884,11 +900,11 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
     int n_global = 0;
     for (int i = 0; i < BH; ++i) n_global += lab[i] ? 0 : 1;
     // chunk table of the new layout, the chunks of a head contiguous
-    const int chunk_threads = pick_chunk_threads(c.prefix_len, c.head_dim, cap);
+    const ChunkPass pass = pick_chunk_pass(c.prefix_len, c.head_dim, cap);
     int n_items = 0;
     for (int i = 0; i < BH; ++i) {
         item_start[i] = n_items;
-        const int nc = chunks_of(c.prefix_len, cap[i], chunk_threads, c.head_dim);
+        const int nc = chunks_of(c.prefix_len, cap[i], pass.threads, c.head_dim, pass.tpr);
         for (int k = 0; k < nc; ++k) items[n_items++] = ((uint32_t)i << 8) | (uint32_t)k;
     }
     item_start[BH] = n_items;
@@ -923,7 +939,8 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
     L.budget.assign(bud, bud + BH);
     L.label_local.assign(lab, lab + BH);
     L.cap.assign(cap.begin(), cap.end());
-    L.chunk_threads = chunk_threads;
+    L.chunk_threads = pass.threads;
+    L.chunk_tpr = pass.tpr;
     L.items = n_items;
     L.n_global = n_global;
     for (int i = 0; i < BH; ++i) L.n[i] = std::min(L.n[i], L.budget[i]);

@@ -192,7 +192,7 @@ struct AttnPlan {
                      // past the head's own length masked (0: none)
     int tpr;         // tokens per row and pass: kAttnTpr, or 3/4 or half of it
                      // (one block per head, every head within that pass), or
-                     // kAttnTprWide
+                     // kAttnTprWide (chunked: 1024 threads)
 };
 // Per-layer pointers of a multi-layer attention launch (up to kMaxLayersPerLaunch).
 constexpr int kMaxLayersPerLaunch = 64;

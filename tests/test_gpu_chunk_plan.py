@@ -1,6 +1,6 @@
 """Attention over chunk tables on both sides of the block-size rule: tables with
-at most one chunk per compute unit (256) at 256, 512 and 1024 threads, one
-chunk more, and more chunks than compute units at every size; the last step of
+at most one chunk per compute unit (256) at 256, 512 and 1024 threads and with
+the wide pass, and one chunk more; the last step of
 a generation that keeps every token, against fp64 attention over all of them."""
 import math
 
@@ -18,7 +18,8 @@ pytestmark = pytest.mark.gpu
     (64, 1, 128),    # 257 of them: 512 threads
     (127, 1, 128),   # 2 of 256 tokens, one head of 3: 255, 512 threads
     (128, 1, 128),   # 257: 1024 threads
-    (250, 20, 128),  # 270 of 512 tokens: fewest rounds
+    (250, 20, 128),  # 270 of 512 tokens, 250 of 576: 1024 threads, wide pass
+    (250, 20, 64),   # the same at d = 64: 270 of 512, 250 of 1024 tokens
     (128, 0, 64),    # 2 of 256 tokens: 256 threads
     (128, 1, 64),    # 257: 512 threads
     (3, 1, 64)])
