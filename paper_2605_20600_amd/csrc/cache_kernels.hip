@@ -430,27 +430,6 @@ __device__ void select_small(double* sig, const uint16_t* order, uint8_t* evict,
     if (q == 0 && c < mq) evict[order[r]] = 1;
 }
 
-// q . k of a cached row in fp64, the dims summed in order, without FMA.
-template <int D>
-__device__ __forceinline__ double dot_row(const double* qd, const uint16_t* row) {
-#pragma clang fp contract(off)
-    const uint4* kr = reinterpret_cast<const uint4*>(row);
-    uint4 v[D / 8];
-#pragma unroll
-    for (int c = 0; c < D / 8; ++c) v[c] = kr[c];
-    double acc = 0.0;
-#pragma unroll
-    for (int c = 0; c < D / 8; ++c) {
-        const uint32_t wv[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc = acc + qd[8 * c + 2 * e] * (double)bf_lo(wv[e]);
-            acc = acc + qd[8 * c + 2 * e + 1] * (double)bf_hi(wv[e]);
-        }
-    }
-    return acc;
-}
-
 // The attention-sum variant of the eviction score (the oracle's
 // ORC_SCORE_ATTN_SUM): for each window query p (steps max(0, step-P+1) ..
 // step, from the query ring), its softmax over the cache it attended -- the
@@ -497,56 +476,103 @@ __device__ __forceinline__ double sum_in_order(const double* w, int len, int com
 
 // One query at a time (periods shorter than a group, caches whose weights for
 // a group do not fit the LDS).  qd: LDS [D]; w: LDS [C + n].
-template <int D, int NT>
+template <int D>
 __device__ void attention_sum_single(const LayerDev& L, const SegPtrs& S, int C, int h, int n,
                                      int r_lo, int r_hi, int step, const uint16_t* order,
                                      const int32_t* pos, double* qd, double* sig, double* w,
                                      double sqrt_d, int tid) {
 #pragma clang fp contract(off)
-    constexpr int WAVES = NT / 64;
+    constexpr int WAVES = kBlock / 64;
     __shared__ double red[WAVES];
-    __shared__ double zsh;
+    __shared__ double msh, zsh;
+    __shared__ int nvs;
     const int P = L.ring_len;
     const int p0 = step - P + 1 > 0 ? step - P + 1 : 0;
     const int lane = tid & 63, wave = tid >> 6;
-    for (int r = r_lo + tid; r < r_hi; r += NT) sig[r] = 0.0;
+    for (int r = r_lo + tid; r < r_hi; r += kBlock) sig[r] = 0.0;
     for (int p = p0; p <= step; ++p) {
-        for (int i = tid; i < D; i += NT) qd[i] = bf_f64(L.qring[((size_t)h * P + p % P) * D + i]);
-        const int nv = visible(order, pos, n, p), len = C + nv;
+        for (int i = tid; i < D; i += kBlock)
+            qd[i] = bf_f64(L.qring[((size_t)h * P + p % P) * D + i]);
+        if (tid == 0) nvs = visible(order, pos, n, p);
         __syncthreads();
+        const int vis = C + nvs;
         double m = -INFINITY;
-        for (int j = tid; j < len; j += NT) {
+        for (int j = tid; j < vis; j += kBlock) {
             const uint16_t* row =
                 j < C ? S.K + (size_t)j * D : S.K + (size_t)(C + order[j - C]) * D;
-            const double l = dot_row<D>(qd, row) / sqrt_d;
+            const uint4* kr = reinterpret_cast<const uint4*>(row);
+            // the query is read from LDS for every row: an offset of zero the
+            // compiler cannot see through keeps it from hoisting all D values
+            // out of the loop.  The values of the next T dims are read while
+            // this T dims' products are added (a scheduling barrier keeps the
+            // reads a stage ahead).
+            int zo;
+            asm volatile("s_mov_b32 %0, 0" : "=s"(zo));
+            const double* qz = qd + zo;
+            constexpr int T = 4;
+            double acc = 0.0, qa[T], qb[T];
+#pragma unroll
+            for (int e = 0; e < T; ++e) qa[e] = qz[e];
+            constexpr int HR = D / 16;  // half a row in flight at a time
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                uint4 v[HR];
+#pragma unroll
+                for (int c = 0; c < HR; ++c) v[c] = kr[half * HR + c];
+#pragma unroll
+                for (int c = 0; c < HR; ++c) {
+                    const uint32_t wv[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
+#pragma unroll
+                    for (int st = 0; st < 8 / T; ++st) {
+                        const int i0 = 8 * (half * HR + c) + st * T;  // first dim of the stage
+                        if (i0 + T < D) {
+#pragma unroll
+                            for (int e = 0; e < T; ++e) qb[e] = qz[i0 + T + e];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int e = 0; e < T; ++e) {
+                            const int k = st * T + e;  // dim within the 16-byte chunk
+                            acc = fma(qa[e],
+                                      (double)((k & 1) ? bf_hi(wv[k / 2]) : bf_lo(wv[k / 2])), acc);
+                        }
+#pragma unroll
+                        for (int e = 0; e < T; ++e) qa[e] = qb[e];
+                    }
+                }
+            }
+            const double l = acc / sqrt_d;
             w[j] = l;
             m = fmax(m, l);
         }
         for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
         if (lane == 0) red[wave] = m;
         __syncthreads();
-        m = red[0];
-        for (int i = 1; i < WAVES; ++i) m = fmax(m, red[i]);
-        for (int j = tid; j < len; j += NT) w[j] = exp(w[j] - m);
+        if (tid == 0) {
+            double mx = red[0];
+            for (int i = 1; i < WAVES; ++i) mx = fmax(mx, red[i]);
+            msh = mx;
+        }
+        __syncthreads();
+        for (int j = tid; j < vis; j += kBlock) w[j] = exp(w[j] - msh);
         __syncthreads();
         if (tid == 0) {  // normaliser, summed over the query's cache in order
             double z = 0.0;
             int j = 0;
             // the reads go out eight at a time, the additions stay in order
-            for (; j + 8 <= len; j += 8) {
+            for (; j + 8 <= vis; j += 8) {
                 double t[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) t[u] = w[j + u];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) z += t[u];
             }
-            for (; j < len; ++j) z += w[j];
+            for (; j < vis; ++j) z += w[j];
             zsh = z;
         }
         __syncthreads();
-        const double z = zsh;
-        for (int r = r_lo + tid; r < r_hi && r < nv; r += NT) sig[r] = sig[r] + w[C + r] / z;
-        __syncthreads();  // qd, w, red and zsh are rewritten for the next query
+        for (int r = r_lo + tid; r < r_hi && r < nvs; r += kBlock) sig[r] = sig[r] + w[C + r] / zsh;
+        __syncthreads();  // qd, w, nvs, red, msh and zsh are rewritten for the next query
     }
 }
 
@@ -867,7 +893,8 @@ __device__ __forceinline__ int update_block(const LayerDev& L, int C, int N, con
                 attention_sum_group<D, NT>(L, S, C, h, n, r_lo, r_hi, step, order, pos, sig, qs,
                                            UpdateLds::weight_stride(C, lds_cap), group, sqrt_d, tid);
             } else if constexpr (SCORES == kScoresAttnSingle) {
-                attention_sum_single<D, NT>(
+                static_assert(NT == kBlock, "single queries run in 256-thread blocks");
+                attention_sum_single<D>(
                     L, S, C, h, n, r_lo, r_hi, step, order, pos, qs, sig,
                     reinterpret_cast<double*>(lds + UpdateLds::off_w(N, lds_cap, D)), sqrt_d, tid);
             } else {
