@@ -91,9 +91,12 @@ __global__ __launch_bounds__(kBlock) void k_score(LayerDev L, const uint16_t* q,
     const unsigned char* tile = lds + wave * PER * ROWB;
     const uint32_t tile0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds +
                            wave * PER * ROWB;
-    auto load_rows = [&](int r0) {  // this wavefront's rows, those past the end the last again
+    // this wavefront's rows; those past the end are the last again, or left as
+    // they are (their logits are not kept)
+    auto load_rows = [&](int r0) {
 #pragma unroll
         for (int i = 0; i < R * CH; ++i) {
+            if (r0 + i * (64 / CH) >= len) break;
             const int p = i * 64 + lane, row = p / CH, c = (p % CH) ^ swizzle<D>(row);
             load_to_lds(K + (size_t)min(r0 + row, len - 1) * D + c * 8, tile0 + i * 1024);
         }
