@@ -49,3 +49,23 @@ def test_prefill_tiles(C, batch, heads, d):
     w = torch.softmax((k1 * q1[:, :, None]).sum(-1) / math.sqrt(d), -1)
     # fp32 logits, weights and sums of up to C + 1 terms
     assert float((dec - (w[..., None] * v1).sum(2)).abs().max()) <= 2e-5 * float(v1.abs().max())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_prefill_later_infinities(d):
+    # infinite values and NaN keys at token 40 and from 96 on stay out of the
+    # rows of earlier groups of 32 queries, wherever the key tiles of 64 end
+    C, heads = 130, 3
+    wl = W.LUMINA768.with_(batch=1, heads=heads, layers=1, head_dim=d, prefix_len=C, grid_rows=2,
+                           grid_cols=4, period=5, group_threshold=5)
+    inp = DeviceInputs(wl)
+    sess = new_session(wl)
+    ref = sess.prefill_attn(0, inp.qc[0], inp.kc[0], inp.vc[0])
+    for first in (40, 96, 129):
+        kc, vc = inp.kc[0].clone(), inp.vc[0].clone()
+        vc[:, :, first:] = math.inf
+        kc[:, :, first:] = math.nan
+        out = sess.prefill_attn(0, inp.qc[0], kc, vc)
+        clean = first // 32 * 32
+        assert torch.equal(out[:, :, :clean], ref[:, :, :clean])
+        assert not bool(torch.isfinite(out[:, :, first:]).any())
