@@ -69,3 +69,27 @@ def test_prefill_later_infinities(d):
         clean = first // 32 * 32
         assert torch.equal(out[:, :, :clean], ref[:, :, :clean])
         assert not bool(torch.isfinite(out[:, :, first:]).any())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("log2q", [4, 12, 20, 40])
+def test_prefill_large_scores(log2q, sign, d):
+    # scores of 2^15 to 2^51 in log2 units: a last place of the larger ones is
+    # worth more than exp2's whole range.  The dot products are exact in fp32
+    # (8-bit keys times a power of two), and two keys' scores are at least 184
+    # apart, so each row takes one value, that of its largest key so far.
+    C, heads = 120, 3
+    wl = W.LUMINA768.with_(batch=1, heads=heads, layers=1, head_dim=d, prefix_len=C, grid_rows=2,
+                           grid_cols=4, period=5, group_threshold=5)
+    gen = torch.Generator().manual_seed(7)
+    c = torch.stack([torch.randperm(C, generator=gen) for _ in range(heads)])
+    c = (sign * (128 + c).float()).cuda()
+    kc = c[None, :, :, None].expand(1, heads, C, d).bfloat16().contiguous()
+    qc = torch.full((1, heads, C, d), 2.0 ** log2q, device="cuda").bfloat16()
+    vc = torch.randn((1, heads, C, d), generator=gen).cuda().bfloat16()
+    out = new_session(wl).prefill_attn(0, qc, kc, vc)
+    first = c.cummax(1).indices[None, :, :, None].expand(1, heads, C, d)
+    ref = torch.gather(vc.float(), 2, first)
+    # one weight w, and its inverse: w v exact, 1 / w and the product rounded
+    assert float((out - ref).abs().max()) <= 2.0 ** -22 * float(vc.abs().max())
