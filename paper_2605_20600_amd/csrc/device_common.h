@@ -89,22 +89,27 @@ __device__ __forceinline__ int swizzle(int row) {
 // 16 bytes per lane from memory into LDS at dst + 16 * lane (dst: the
 // wavefront's, a byte offset in LDS).  As asm, since the compiler would wait
 // for the next tile's loads in front of this tile's reads; the caller waits
-// (lds_loads_done) before the barrier after which the tile is read.  Nothing
-// else here uses m0 (LDS instructions of gfx950 do not).
+// (lds_loads_done) before the barrier after which the tile is read.  m0 is named
+// as clobbered: it is a reserved register, so the compiler warns that it will
+// not keep its value, which is what is asked for (without it, a builtin load to
+// LDS behind this one may reuse the m0 of one before).
 // ONCE: the rows are read by no other block (non-temporal).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <bool ONCE = false>
 __device__ __forceinline__ void load_to_lds(const uint16_t* src, uint32_t dst) {
     if constexpr (ONCE)
         asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
                      :
                      : "v"(src), "s"(dst)
-                     : "memory");
+                     : "memory", "m0");
     else
         asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                      :
                      : "v"(src), "s"(dst)
-                     : "memory");
+                     : "memory", "m0");
 }
+#pragma clang diagnostic pop
 __device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 struct SegPtrs {
