@@ -302,6 +302,9 @@ void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
 #pragma unroll
             for (int g = 0; g < 4; ++g)
                 ob[j * OP + ((8 * mb + 2 * g + half) ^ (j & (OP - 1)))] = piece(mb, g);
+        // rows other lanes of this wavefront wrote: no read moves above here
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int i = 0; i < OP / 2; ++i) {
             const int row = (i * 64 + lane) / OP, c = lane & (OP - 1);
