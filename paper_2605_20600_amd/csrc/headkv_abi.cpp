@@ -236,7 +236,9 @@ LayerDev dev_of(headkv_t h, const Layer& L) {
 // exchange budgets and tables.  A call takes a buffer and gives it back when the
 // stream has been waited for, so none is in use by the GPU outside a call.
 // Buffers that are not in use are kept for the next call (pinning one takes
-// longer than the call): at most kKept of them, of at most kKeptBytes each.
+// longer than the call): at most kKept of them, all of kKeptBytes, so that any
+// kept one serves any call that needs no more (pinning 1 MiB takes as long as
+// 64 KiB, 10 to 50 us).
 class Stage {
   public:
     Stage() = default;
@@ -244,27 +246,24 @@ class Stage {
     Stage& operator=(const Stage&) = delete;
     ~Stage() {
         if (!p_) return;
-        if (bytes_ <= kKeptBytes) {
+        if (bytes_ == kKeptBytes) {
             std::lock_guard<std::mutex> lock(pool().mutex);
             if (pool().n < kKept) {
-                pool().kept[pool().n++] = {p_, bytes_};
+                pool().kept[pool().n++] = p_;
                 return;
             }
         }
         (void)hipHostFree(p_);
     }
     int take(size_t bytes) {
-        {
+        bytes_ = std::max(bytes, kKeptBytes);
+        if (bytes_ == kKeptBytes) {
             std::lock_guard<std::mutex> lock(pool().mutex);
-            for (int i = 0; i < pool().n; ++i) {
-                if (pool().kept[i].bytes < bytes) continue;
-                p_ = pool().kept[i].p;
-                bytes_ = pool().kept[i].bytes;
-                pool().kept[i] = pool().kept[--pool().n];
+            if (pool().n > 0) {
+                p_ = pool().kept[--pool().n];
                 return 0;
             }
         }
-        bytes_ = align_up(bytes, 1 << 16);
         // allowed while another thread captures a graph
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         (void)hipThreadExchangeStreamCaptureMode(&mode);
@@ -278,13 +277,9 @@ class Stage {
   private:
     static constexpr int kKept = 4;
     static constexpr size_t kKeptBytes = 1 << 20;
-    struct Buffer {
-        void* p;
-        size_t bytes;
-    };
     struct Pool {
         std::mutex mutex;
-        Buffer kept[kKept];
+        void* kept[kKept];
         int n = 0;
     };
     static Pool& pool() {

@@ -1,0 +1,135 @@
+"""The host side of headkv_assign_budgets on the CPU: csrc/headkv_abi.cpp built
+against tests/host/fake_hip.cpp, which stands in for the HIP runtime and the
+kernels and counts pinned allocations and frees."""
+import ctypes
+import os
+import shutil
+import subprocess
+import threading
+
+import numpy as np
+import pytest
+
+from paper_2605_20600_amd import binding as B
+from paper_2605_20600_amd.build import CSRC
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+N = 4500  # num_visual
+
+
+class Counts(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_long) for n in ("mallocs", "frees", "unsafe_calls", "copies",
+                                             "live_buffers", "live_bytes", "max_live")]
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    lib = tmp_path_factory.mktemp("fake") / "libheadkv_fake.so"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-pthread",
+                    "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
+                    os.path.join(HERE, "host", "fake_hip.cpp"),
+                    os.path.join(CSRC, "headkv_abi.cpp"), "-Wl,-z,defs", "-o", str(lib)],
+                   check=True)
+    return lib
+
+
+@pytest.fixture
+def fake(built, tmp_path, monkeypatch):
+    # a copy of its own: the library keeps its pinned buffers until the process ends
+    path = tmp_path / "libheadkv.so"
+    shutil.copy(built, path)
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "LIB_PATH", str(path))
+    lib = B.load()
+    lib.fake_counts.restype = Counts
+    lib.fake_last_host.restype = ctypes.c_void_p
+    return lib
+
+
+def _buffer(n):
+    a = np.zeros(n + 256, np.uint8)
+    return a[-a.ctypes.data % 256:][:n]
+
+
+class Handle:
+    """A one-layer handle at its grouping step (group_threshold 1)."""
+
+    def __init__(self, batch, strategy=B.HEADKV_ATTN_VARLEN):
+        self.cfg = B.HeadKVConfig(
+            batch=batch, num_layers=1, num_heads=8, head_dim=64, prefix_len=0, row_len=10,
+            num_visual=N, recent_len=20, local_window=20, period=1, group_threshold=1,
+            budget_mode=B.HEADKV_BUDGET_OVERRIDE, rho_num=1, rho_den=2, rs_num=1, rs_den=2,
+            attn_strategy=strategy, score_mode=0, cfg_pairs=0, tau=0.9)
+        self.BH = 8 * batch
+        self.sizes = B.headkv_plan(self.cfg)
+        self.dense, self.meta, self.ws = (_buffer(n) for n in self.sizes)
+        self.h = B.headkv_create(self.cfg, [self.dense.ctypes.data], [self.meta.ctypes.data],
+                                 self.ws.ctypes.data)
+        B.headkv_prefill(self.h, 0, None, None)
+        row = _buffer(self.BH * 64 * 2).ctypes.data
+        B.headkv_append_and_evict(self.h, 0, 0, row, row, row)
+        self.labels = np.zeros(self.BH, np.uint8)
+        self.budgets = np.zeros(self.BH, np.int32)
+        rng = np.random.default_rng(batch)
+        self.override = rng.integers(1, N + 1, self.BH).astype(np.int32)
+
+    def size(self):
+        """The sizing call: (status, bytes needed)."""
+        return B.headkv_assign_budgets(self.h, 0, self.labels.ctypes.data,
+                                       self.override.ctypes.data, self.budgets.ctypes.data,
+                                       None, 0)
+
+    def assign(self):
+        """The whole call, into a segment buffer that the fake kernels do not touch."""
+        st, need = B.headkv_assign_budgets(self.h, 0, self.labels.ctypes.data,
+                                           self.override.ctypes.data, self.budgets.ctypes.data,
+                                           0x7F0000000000, 1 << 62)
+        assert st == B.HEADKV_OK, B.headkv_last_error()
+        self.check_tables(need)
+
+    def check_tables(self, need):
+        BH, at = self.BH, [0]
+
+        def take(dtype, n):
+            a = self.meta[at[0]:at[0] + n * np.dtype(dtype).itemsize].view(dtype)
+            at[0] = (at[0] + a.nbytes + 255) // 256 * 256
+            return a
+
+        seg_off, cap = take(np.int64, BH), take(np.int32, BH)
+        for _ in range(2):  # lengths, budgets
+            take(np.int32, BH)
+        take(np.int32, BH)  # n*
+        take(np.int32, BH)  # labels
+        order = take(np.int32, BH)
+        # room for every head at its largest, in chunks of 256 tokens
+        items, item_start = take(np.uint32, BH * ((N + 1 + 255) // 256)), take(np.int32, BH + 1)
+        want_cap = np.minimum(self.override + 1, N)
+        assert (self.budgets == self.override).all() and (cap == want_cap).all()
+        seg = (2 * want_cap.astype(np.int64) * 64 * 2 + want_cap * 4 + 255) // 256 * 256
+        assert need == seg.sum() and (seg_off == np.cumsum(seg) - seg).all()
+        if self.cfg.attn_strategy == B.HEADKV_ATTN_GROUPED:
+            assert (order == np.argsort(self.override & 1, kind="stable")).all()
+        else:
+            assert (order == np.argsort(-want_cap, kind="stable")).all()
+        n = np.diff(item_start)
+        assert item_start[0] == 0 and (n >= 1).all()
+        head = np.repeat(np.arange(BH), n)
+        chunk = np.arange(item_start[-1]) - np.repeat(item_start[:-1], n)
+        assert (items[:item_start[-1]] == head * 256 + chunk).all()
+
+
+def test_growing_handles_pin_once(fake):
+    # handles whose tables need ever more room: after the first call every one
+    # finds a kept buffer that is large enough
+    handles = [Handle(batch) for batch in (64, 128, 256, 384, 512, 640, 768)]
+    for h in handles:
+        h.size()
+    before = fake.fake_counts().mallocs
+    for _ in range(3):
+        for h in handles:
+            assert h.size()[0] == B.HEADKV_ERR_CAPACITY
+    c = fake.fake_counts()
+    assert (c.mallocs - before, c.frees) == (0, 0)
+    for h in handles:
+        h.assign()
