@@ -216,9 +216,9 @@ __global__ __launch_bounds__(kBlock) void k_score(LayerDev L, const uint16_t* q,
 // ------------------------------------------------------------------ budgets
 // With cfg_pairs, batch rows 2i (conditional) and 2i+1 (unconditional) form a
 // guidance pair and both take the labels of row 2i.
-// host: pinned host memory, budgets then labels [BH] each, which the host reads
-// once the kernel has ended: two device-to-host copies of a few hundred bytes
-// took as long as the grouping kernel.
+// host: nullptr, or pinned host memory, budgets then labels [BH] each, which the
+// host reads once the kernel has ended: two device-to-host copies of a few
+// hundred bytes took as long as the grouping kernel.
 __global__ void k_budgets(LayerDev L, int H, int N, const uint8_t* is_local,
                           const int32_t* override_b, int32_t* budgets, int mode, int row_len,
                           int recent_len, int rho_num, int rho_den, int cfg_pairs,
@@ -249,8 +249,10 @@ __global__ void k_budgets(LayerDev L, int H, int N, const uint8_t* is_local,
     budgets[idx] = B;
     L.budget[idx] = B;
     L.label[idx] = loc;
-    host[idx] = B;
-    host[(int)(gridDim.x * blockDim.x) + idx] = loc;
+    if (host) {
+        host[idx] = B;
+        host[(int)(gridDim.x * blockDim.x) + idx] = loc;
+    }
 }
 
 // The tables of the new layout from pinned host memory into the metadata, in

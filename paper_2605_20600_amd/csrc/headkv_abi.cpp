@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -236,17 +237,19 @@ LayerDev dev_of(headkv_t h, const Layer& L) {
 // exchange budgets and tables.  A call takes a buffer and gives it back when the
 // stream has been waited for, so none is in use by the GPU outside a call.
 // Buffers that are not in use are kept for the next call (pinning one takes
-// longer than the call): at most kKept of them, all of kKeptBytes, so that any
-// kept one serves any call that needs no more (pinning 1 MiB takes as long as
-// 64 KiB, 10 to 50 us).
+// longer than the call): at most kKept of them, all of kBytes, so that any one
+// serves any call (pinning 1 MiB takes as long as 64 KiB, 10 to 50 us).  What
+// does not fit (the tables of 10,000 to 30,000 heads, by their chunks) goes
+// through plain memory and copies.
 class Stage {
   public:
+    static constexpr size_t kBytes = 1 << 20;
     Stage() = default;
     Stage(const Stage&) = delete;
     Stage& operator=(const Stage&) = delete;
     ~Stage() {
         if (!p_) return;
-        if (bytes_ == kKeptBytes) {
+        {
             std::lock_guard<std::mutex> lock(pool().mutex);
             if (pool().n < kKept) {
                 pool().kept[pool().n++] = p_;
@@ -255,9 +258,8 @@ class Stage {
         }
         (void)hipHostFree(p_);
     }
-    int take(size_t bytes) {
-        bytes_ = std::max(bytes, kKeptBytes);
-        if (bytes_ == kKeptBytes) {
+    int take() {
+        {
             std::lock_guard<std::mutex> lock(pool().mutex);
             if (pool().n > 0) {
                 p_ = pool().kept[--pool().n];
@@ -267,7 +269,7 @@ class Stage {
         // allowed while another thread captures a graph
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         (void)hipThreadExchangeStreamCaptureMode(&mode);
-        const hipError_t e = hipHostMalloc(&p_, bytes_, hipHostMallocPortable | hipHostMallocCoherent);
+        const hipError_t e = hipHostMalloc(&p_, kBytes, hipHostMallocPortable | hipHostMallocCoherent);
         (void)hipThreadExchangeStreamCaptureMode(&mode);
         if (e != hipSuccess) p_ = nullptr;
         return (int)e;
@@ -276,7 +278,6 @@ class Stage {
 
   private:
     static constexpr int kKept = 4;
-    static constexpr size_t kKeptBytes = 1 << 20;
     struct Pool {
         std::mutex mutex;
         void* kept[kKept];
@@ -287,8 +288,17 @@ class Stage {
         return p;
     }
     void* p_ = nullptr;
-    size_t bytes_ = 0;
 };
+
+headkv_status plain_memory(size_t bytes, std::unique_ptr<char[]>* p) {
+    p->reset(new (std::nothrow) char[bytes]);
+    return *p ? ok() : fail(HEADKV_ERR_INVALID_ARG, "out of host memory");
+}
+
+template <typename T>
+headkv_status copy(T* dst, const T* src, int n, hipMemcpyKind kind, hipStream_t s, const char* what) {
+    return hip_status(hipMemcpyAsync(dst, src, sizeof(T) * (size_t)n, kind, s), what);
+}
 
 // Event pair for a sampled launch of `kind`, or nullptrs.
 void take_events(headkv_t h, bool time_it, int kind, double bytes, void** e0, void** e1) {
@@ -841,28 +851,28 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
     const int BH = h->shape.BH;
     hipStream_t s = (hipStream_t)stream;
     LayerDev Dold = dev_of(h, L);
-    // budgets and labels [BH] int32 each; then the tables: offsets [BH] int64,
-    // capacities and order [BH], first entries [BH + 1], entries
+    // budgets and labels [BH] int32 each, written by the kernel into a stage or
+    // copied into plain memory
     const size_t tables_at = align_up(2 * sizeof(int32_t) * BH, 256);
     Stage stage;
-    st = hip_status(stage.take(tables_at + sizeof(int64_t) * BH + sizeof(int32_t) * (3 * (size_t)BH + 1) +
-                               sizeof(uint32_t) * (size_t)h->ml.max_items),
-                    "staging memory");
+    std::unique_ptr<char[]> plain_read, plain_tables;
+    const bool staged = tables_at <= Stage::kBytes;
+    if (staged)
+        st = hip_status(stage.take(), "staging memory");
+    else
+        st = plain_memory(tables_at, &plain_read);
     if (st) return st;
-    int32_t* bud = reinterpret_cast<int32_t*>(stage.data());
-    const int32_t* lab = bud + BH;  // the labels the budgets used (cfg pairs applied)
+    int32_t* bud = reinterpret_cast<int32_t*>(staged ? stage.data() : plain_read.get());
+    int32_t* lab = bud + BH;  // the labels the budgets used (cfg pairs applied)
     st = hip_status(launch_budgets(Dold, h->shape, is_local, budget_override, budgets, c.budget_mode,
-                                   c.row_len, c.recent_len, c.rho_num, c.rho_den, c.cfg_pairs, bud,
-                                   stream),
+                                   c.row_len, c.recent_len, c.rho_num, c.rho_den, c.cfg_pairs,
+                                   staged ? bud : nullptr, stream),
                     "budget launch");
+    if (!st && !staged) st = copy(bud, budgets, BH, hipMemcpyDeviceToHost, s, "budget read-back");
+    if (!st && !staged) st = copy(lab, Dold.label, BH, hipMemcpyDeviceToHost, s, "label read-back");
     headkv_status st_sync = hip_status(hipStreamSynchronize(s), "stream wait");
     if (st || st_sync) return st ? st : st_sync;
     // segments: prefix + min(budget + P, N) slots each, in head order
-    int64_t* off = reinterpret_cast<int64_t*>(stage.data() + tables_at);
-    int32_t* cap_t = reinterpret_cast<int32_t*>(off + BH);
-    int32_t* order = cap_t + BH;
-    int32_t* item_start = order + BH;
-    uint32_t* items = reinterpret_cast<uint32_t*>(item_start + BH + 1);
     std::vector<int> cap(BH);
     size_t total = 0;
     for (int i = 0; i < BH; ++i) {
@@ -876,14 +886,40 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
         const int cmax = *std::max_element(cap.begin(), cap.end());
         std::fill(cap.begin(), cap.end(), cmax);
     }
-    for (int i = 0; i < BH; ++i) {
-        cap_t[i] = cap[i];
-        off[i] = (int64_t)total;
-        total += segment_bytes(c.prefix_len, cap[i], c.head_dim);
-    }
+    for (int x : cap) total += segment_bytes(c.prefix_len, x, c.head_dim);
     *ragged_bytes_needed = total;
     if (!ragged_kv || ragged_bytes < total)
         return fail(HEADKV_ERR_CAPACITY, "ragged_kv is NULL or smaller than *ragged_bytes_needed");
+    // chunk table of the new layout, the chunks of a head contiguous
+    const ChunkPass pass = pick_chunk_pass(c.prefix_len, c.head_dim, cap);
+    auto chunks = [&](int i) {
+        return chunks_of(c.prefix_len, cap[i], pass.threads, c.head_dim, pass.tpr);
+    };
+    int n_items = 0;
+    for (int i = 0; i < BH; ++i) n_items += chunks(i);
+    // the tables: offsets [BH] int64, capacities and order [BH], first entries
+    // [BH + 1], entries; behind the budgets where the stage has room for them
+    const size_t table_bytes = sizeof(int64_t) * BH + sizeof(int32_t) * (3 * (size_t)BH + 1) +
+                               sizeof(uint32_t) * (size_t)n_items;
+    const bool tables_staged = staged && tables_at + table_bytes <= Stage::kBytes;
+    if (!tables_staged) st = plain_memory(table_bytes, &plain_tables);
+    if (st) return st;
+    int64_t* off = reinterpret_cast<int64_t*>(tables_staged ? stage.data() + tables_at
+                                                            : plain_tables.get());
+    int32_t* cap_t = reinterpret_cast<int32_t*>(off + BH);
+    int32_t* order = cap_t + BH;
+    int32_t* item_start = order + BH;
+    uint32_t* items = reinterpret_cast<uint32_t*>(item_start + BH + 1);
+    total = 0;
+    n_items = 0;
+    for (int i = 0; i < BH; ++i) {
+        off[i] = (int64_t)total;
+        total += segment_bytes(c.prefix_len, cap[i], c.head_dim);
+        cap_t[i] = cap[i];
+        item_start[i] = n_items;
+        for (int k = 0, nc = chunks(i); k < nc; ++k) items[n_items++] = ((uint32_t)i << 8) | (uint32_t)k;
+    }
+    item_start[BH] = n_items;
     // attention dispatch order: longest heads first, so that when a layer
     // needs more than one round of blocks the short heads fill the tail; with
     // HEADKV_ATTN_GROUPED the global heads, then the local heads
@@ -894,21 +930,22 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
         std::stable_sort(order, order + BH, [&](int a, int b) { return cap[a] > cap[b]; });
     int n_global = 0;
     for (int i = 0; i < BH; ++i) n_global += lab[i] ? 0 : 1;
-    // chunk table of the new layout, the chunks of a head contiguous
-    const ChunkPass pass = pick_chunk_pass(c.prefix_len, c.head_dim, cap);
-    int n_items = 0;
-    for (int i = 0; i < BH; ++i) {
-        item_start[i] = n_items;
-        const int nc = chunks_of(c.prefix_len, cap[i], pass.threads, c.head_dim, pass.tpr);
-        for (int k = 0; k < nc; ++k) items[n_items++] = ((uint32_t)i << 8) | (uint32_t)k;
-    }
-    item_start[BH] = n_items;
-    // tables of the new layout (the staging memory outlives the launch: the
-    // stream is waited for below on every path)
+    // tables of the new layout (their host memory outlives the launch or the
+    // copies: the stream is waited for below on every path)
     LayerDev Dnew = make_layer_dev(ragged_kv, L.meta, h->ml);
-    st = hip_status(launch_tables(Dnew, h->shape,
-                                  LayoutTables{off, cap_t, order, item_start, items, n_items}, stream),
-                    "table upload");
+    if (tables_staged) {
+        st = hip_status(launch_tables(Dnew, h->shape,
+                                      LayoutTables{off, cap_t, order, item_start, items, n_items},
+                                      stream),
+                        "table upload");
+    } else {
+        const hipMemcpyKind up = hipMemcpyHostToDevice;
+        st = copy(Dnew.seg_off, off, BH, up, s, "table upload");
+        if (!st) st = copy(Dnew.cap, cap_t, BH, up, s, "table upload");
+        if (!st) st = copy(Dnew.order, order, BH, up, s, "table upload");
+        if (!st) st = copy(Dnew.item_start, item_start, BH + 1, up, s, "table upload");
+        if (!st) st = copy(Dnew.items, items, n_items, up, s, "table upload");
+    }
     // padded rows are read (and masked) by the attention: keep them finite
     if (!st && c.attn_strategy == HEADKV_ATTN_PADDED)
         st = hip_status(hipMemsetAsync(ragged_kv, 0, total, s), "ragged clear");

@@ -146,7 +146,7 @@ int launch_score(const LayerDev& L, const Shape& s, const uint16_t* q, int32_t* 
                  uint8_t* is_local, int len, double sqrt_d, double tau, int local_window,
                  void* stream);
 // Writes budgets and the labels the updates use (L.label) for every head, and
-// both into host (pinned, [2][BH]).
+// both into host (pinned, [2][BH]) unless that is nullptr.
 int launch_budgets(const LayerDev& L, const Shape& s, const uint8_t* is_local,
                    const int32_t* override_b, int32_t* budgets, int mode, int row_len,
                    int recent_len, int rho_num, int rho_den, int cfg_pairs, int32_t* host,

@@ -133,3 +133,22 @@ def test_growing_handles_pin_once(fake):
     assert (c.mallocs - before, c.frees) == (0, 0)
     for h in handles:
         h.assign()
+
+
+@pytest.mark.parametrize("strategy", [B.HEADKV_ATTN_VARLEN, B.HEADKV_ATTN_GROUPED])
+@pytest.mark.parametrize("batch,copies", [
+    (256, 0),            # 2,048 heads: everything through pinned memory
+    (2048, 5),           # 16,384: the five tables do not fit
+    (131072 // 8 + 1, 7)])  # the budgets and labels neither
+def test_large_tables_are_not_pinned_for_the_call(fake, batch, copies, strategy):
+    h = Handle(batch, strategy)
+    h.size()
+    before = fake.fake_counts()
+    for _ in range(3):
+        assert h.size()[0] == B.HEADKV_ERR_CAPACITY
+    c = fake.fake_counts()
+    assert (c.mallocs, c.frees) == (before.mallocs, 0)
+    h.assign()
+    d = fake.fake_counts()
+    assert (d.mallocs, d.frees, d.copies - c.copies) == (before.mallocs, 0, copies)
+    assert d.live_bytes <= 4 << 20
