@@ -86,7 +86,11 @@ void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
     constexpr int QT = 32 * W;      // queries of a block
     constexpr int ROWB = 2 * D;          // bytes of a row
     constexpr int NP = KT * CH / 64;     // 64-piece loads of a tile's K (or V)
-    extern __shared__ __align__(16) unsigned char lds[];  // [buffer][K, V][KT][D]
+    constexpr int TILEB = 2 * KT * ROWB;  // bytes of a buffer, a power of two
+    // [buffer][K, V][KT][D]; one address bit tells the buffers apart (^= TILEB
+    // below), also behind static LDS, if there were any
+    extern __shared__ __align__(1 << 16) unsigned char lds[];
+    static_assert((1 << 16) % (2 * TILEB) == 0, "a buffer is one address bit");
     const int tiles = (C + QT - 1) / QT;
     // the longest query tiles first; the tiles of a head are nheads blocks
     // apart, so with a multiple of 8 heads they share an XCD's L2
@@ -148,7 +152,6 @@ void k_prefill_attn(LayerDev L, int nheads, const uint16_t* __restrict__ qc,
     // 4 (lane & 3) of a 32-dim block
     const int l16 = lane & 15, vrow = 4 * half + (l16 >> 2);
     const int vpiece = 2 * ((lane >> 4) & 1) + ((l16 & 3) >> 1);
-    constexpr int TILEB = 2 * KT * ROWB;  // bytes of a buffer, a power of two
     typedef __attribute__((address_space(3))) bf16x8_t* lds8_t;
     typedef __attribute__((address_space(3))) bf16x4_t* lds4_t;
     uint32_t ka[KS], va[MB][2];
