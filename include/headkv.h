@@ -23,8 +23,8 @@
  *   - Memory: the caller allocates every device buffer (sizes from headkv_plan
  *     and headkv_assign_budgets) and keeps it alive while the handle uses it.
  *     The library calls no hipMalloc.  Device buffers must be 256-byte aligned.
- *     headkv_assign_budgets takes pinned host memory for the call and keeps at
- *     most four buffers of 1 MiB for the next ones, until the process ends.
+ *     headkv_assign_budgets takes pinned host memory for the call: at most four
+ *     buffers of 1 MiB per process, kept until it ends.
  *   - Streams: `stream` is a hipStream_t (NULL = the default stream).  Calls
  *     are asynchronous on it, except headkv_assign_budgets, which waits for the
  *     stream once to read the budgets back.

@@ -237,9 +237,11 @@ LayerDev dev_of(headkv_t h, const Layer& L) {
 // exchange budgets and tables.  A call takes a buffer and gives it back when the
 // stream has been waited for, so none is in use by the GPU outside a call.
 // Buffers that are not in use are kept for the next call (pinning one takes
-// longer than the call): at most kKept of them, all of kBytes, so that any one
-// serves any call (pinning 1 MiB takes as long as 64 KiB, 10 to 50 us).  What
-// does not fit (the tables of 10,000 to 30,000 heads, by their chunks) goes
+// longer than the call), and none is ever freed: a free waits for the whole
+// device, and is refused while another thread captures a graph.  So there are at
+// most kMost, all of kBytes, so that any one serves any call (pinning 1 MiB
+// takes as long as 64 KiB, 10 to 50 us).  Calls at once beyond those, and what
+// does not fit (the tables of 10,000 to 30,000 heads, by their chunks), go
 // through plain memory and copies.
 class Stage {
   public:
@@ -249,15 +251,10 @@ class Stage {
     Stage& operator=(const Stage&) = delete;
     ~Stage() {
         if (!p_) return;
-        {
-            std::lock_guard<std::mutex> lock(pool().mutex);
-            if (pool().n < kKept) {
-                pool().kept[pool().n++] = p_;
-                return;
-            }
-        }
-        (void)hipHostFree(p_);
+        std::lock_guard<std::mutex> lock(pool().mutex);
+        pool().kept[pool().n++] = p_;
     }
+    // Afterwards data() is the buffer, or nullptr where every one is in use.
     int take() {
         {
             std::lock_guard<std::mutex> lock(pool().mutex);
@@ -265,23 +262,29 @@ class Stage {
                 p_ = pool().kept[--pool().n];
                 return 0;
             }
+            if (pool().made == kMost) return 0;
+            ++pool().made;
         }
         // allowed while another thread captures a graph
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         (void)hipThreadExchangeStreamCaptureMode(&mode);
         const hipError_t e = hipHostMalloc(&p_, kBytes, hipHostMallocPortable | hipHostMallocCoherent);
         (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (e != hipSuccess) p_ = nullptr;
+        if (e != hipSuccess) {
+            p_ = nullptr;
+            std::lock_guard<std::mutex> lock(pool().mutex);
+            --pool().made;
+        }
         return (int)e;
     }
     char* data() const { return static_cast<char*>(p_); }
 
   private:
-    static constexpr int kKept = 4;
+    static constexpr int kMost = 4;
     struct Pool {
         std::mutex mutex;
-        void* kept[kKept];
-        int n = 0;
+        void* kept[kMost];
+        int n = 0, made = 0;
     };
     static Pool& pool() {
         static Pool& p = *new Pool;  // outlives every handle
@@ -856,11 +859,10 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
     const size_t tables_at = align_up(2 * sizeof(int32_t) * BH, 256);
     Stage stage;
     std::unique_ptr<char[]> plain_read, plain_tables;
-    const bool staged = tables_at <= Stage::kBytes;
-    if (staged)
-        st = hip_status(stage.take(), "staging memory");
-    else
-        st = plain_memory(tables_at, &plain_read);
+    if (tables_at <= Stage::kBytes) st = hip_status(stage.take(), "staging memory");
+    if (st) return st;
+    const bool staged = stage.data() != nullptr;
+    if (!staged) st = plain_memory(tables_at, &plain_read);
     if (st) return st;
     int32_t* bud = reinterpret_cast<int32_t*>(staged ? stage.data() : plain_read.get());
     int32_t* lab = bud + BH;  // the labels the budgets used (cfg pairs applied)

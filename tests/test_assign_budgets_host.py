@@ -152,3 +152,28 @@ def test_large_tables_are_not_pinned_for_the_call(fake, batch, copies, strategy)
     d = fake.fake_counts()
     assert (d.mallocs, d.frees, d.copies - c.copies) == (before.mallocs, 0, copies)
     assert d.live_bytes <= 4 << 20
+
+
+def test_calls_at_once_free_nothing(fake):
+    # six calls that hold their buffers at the same time: nothing is freed (a
+    # free waits for the whole device, and is refused while another thread
+    # captures a graph), and the calls beyond the four buffers copy
+    n = 6
+    handles = [Handle(64) for _ in range(n)]
+    all_in = threading.Barrier(n)
+    hook = ctypes.CFUNCTYPE(None)(lambda: all_in.wait(30) and None)
+    for _ in range(3):
+        fake.fake_on_budgets(hook)
+        got = [None] * n
+        threads = [threading.Thread(target=lambda i=i: got.__setitem__(i, handles[i].size()))
+                   for i in range(n)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join(60)
+        fake.fake_on_budgets(ctypes.CFUNCTYPE(None)())
+        assert [g[0] for g in got] == n * [B.HEADKV_ERR_CAPACITY]
+    for h in handles:
+        h.assign()
+    c = fake.fake_counts()
+    assert (c.unsafe_calls, c.frees, c.mallocs, c.max_live) == (0, 0, 4, 4)
