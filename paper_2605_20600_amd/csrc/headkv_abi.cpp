@@ -278,6 +278,9 @@ class Stage {
         return (int)e;
     }
     char* data() const { return static_cast<char*>(p_); }
+    // The stream could not be waited for: the buffer is not used again (and
+    // still counts towards kMost).
+    void leave() { p_ = nullptr; }
 
   private:
     static constexpr int kMost = 4;
@@ -873,6 +876,7 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
     if (!st && !staged) st = copy(bud, budgets, BH, hipMemcpyDeviceToHost, s, "budget read-back");
     if (!st && !staged) st = copy(lab, Dold.label, BH, hipMemcpyDeviceToHost, s, "label read-back");
     headkv_status st_sync = hip_status(hipStreamSynchronize(s), "stream wait");
+    if (st_sync) stage.leave();
     if (st || st_sync) return st ? st : st_sync;
     // segments: prefix + min(budget + P, N) slots each, in head order
     std::vector<int> cap(BH);
@@ -961,6 +965,7 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
                         "relayout launch");
     }
     headkv_status st_wait = hip_status(hipStreamSynchronize(s), "stream wait");
+    if (st_wait) stage.leave();
     if (st || st_wait) {
         // the metadata may already describe the per-head segments while the
         // move into them did not run: nothing may use this layer until it is

@@ -22,7 +22,7 @@ struct Counts {
 } counts;
 size_t live_bytes = 0;
 bool pin_fails = false;
-int fail_waits = 0;             // the next stream waits to fail
+int fail_wait = 0;              // which of the next stream waits fails (1: the next)
 const void* last_host = nullptr;  // where the last k_budgets wrote for the host
 void (*on_budgets)() = nullptr;
 thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
@@ -43,7 +43,7 @@ Counts fake_counts() {
     return c;
 }
 void fake_pin_fails(int yes) { pin_fails = yes != 0; }
-void fake_fail_waits(int n) { fail_waits = n; }
+void fake_fail_wait(int n) { fail_wait = n; }
 const void* fake_last_host() { return last_host; }
 void fake_on_budgets(void (*f)()) { on_budgets = f; }
 
@@ -75,11 +75,7 @@ hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) {
-    if (fail_waits > 0) {
-        --fail_waits;
-        return hipErrorStreamCaptureUnsupported;
-    }
-    return hipSuccess;
+    return fail_wait > 0 && --fail_wait == 0 ? hipErrorStreamCaptureUnsupported : hipSuccess;
 }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t) {
     std::lock_guard<std::mutex> lock(mu);

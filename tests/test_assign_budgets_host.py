@@ -177,3 +177,22 @@ def test_calls_at_once_free_nothing(fake):
         h.assign()
     c = fake.fake_counts()
     assert (c.unsafe_calls, c.frees, c.mallocs, c.max_live) == (0, 0, 4, 4)
+
+
+@pytest.mark.parametrize("waits", [1, 2])
+def test_buffer_of_a_stream_not_waited_for_is_not_used_again(fake, waits):
+    # a stream that cannot be waited for (one that captures, for instance) may
+    # still run the kernel that writes the buffer
+    h = Handle(64)
+    fake.fake_fail_wait(waits)  # the one for the budgets, or the one for the move
+    with pytest.raises(B.HeadKVError) as e:
+        h.assign()
+    assert e.value.status == B.HEADKV_ERR_HIP
+    lost = fake.fake_last_host()
+    assert lost
+    g = Handle(64)
+    for _ in range(3):
+        assert g.size()[0] == B.HEADKV_ERR_CAPACITY
+        assert fake.fake_last_host() != lost
+    g.assign()
+    assert fake.fake_counts().frees == 0
