@@ -240,9 +240,9 @@ LayerDev dev_of(headkv_t h, const Layer& L) {
 // longer than the call), and none is ever freed: a free waits for the whole
 // device, and is refused while another thread captures a graph.  So there are at
 // most kMost, all of kBytes, so that any one serves any call (pinning 1 MiB
-// takes as long as 64 KiB, 10 to 50 us).  Calls at once beyond those, and what
-// does not fit (the tables of 10,000 to 30,000 heads, by their chunks), go
-// through plain memory and copies.
+// takes as long as 64 KiB, 10 to 50 us).  Calls at once beyond those, calls that
+// get no pinned memory, and what does not fit (the tables of 10,000 to 30,000
+// heads, by their chunks) go through plain memory and copies.
 class Stage {
   public:
     static constexpr size_t kBytes = 1 << 20;
@@ -254,15 +254,15 @@ class Stage {
         std::lock_guard<std::mutex> lock(pool().mutex);
         pool().kept[pool().n++] = p_;
     }
-    // Afterwards data() is the buffer, or nullptr where every one is in use.
-    int take() {
+    // Afterwards data() is the buffer, or nullptr where there is none to be had.
+    void take() {
         {
             std::lock_guard<std::mutex> lock(pool().mutex);
             if (pool().n > 0) {
                 p_ = pool().kept[--pool().n];
-                return 0;
+                return;
             }
-            if (pool().made == kMost) return 0;
+            if (pool().made == kMost) return;
             ++pool().made;
         }
         // allowed while another thread captures a graph
@@ -270,12 +270,11 @@ class Stage {
         (void)hipThreadExchangeStreamCaptureMode(&mode);
         const hipError_t e = hipHostMalloc(&p_, kBytes, hipHostMallocPortable | hipHostMallocCoherent);
         (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (e != hipSuccess) {
-            p_ = nullptr;
-            std::lock_guard<std::mutex> lock(pool().mutex);
-            --pool().made;
-        }
-        return (int)e;
+        if (e == hipSuccess) return;
+        (void)hipGetLastError();  // not the next launch's
+        p_ = nullptr;
+        std::lock_guard<std::mutex> lock(pool().mutex);
+        --pool().made;
     }
     char* data() const { return static_cast<char*>(p_); }
     // The stream could not be waited for: the buffer is not used again (and
@@ -862,8 +861,7 @@ headkv_status headkv_assign_budgets(headkv_t h, int32_t layer, const uint8_t* is
     const size_t tables_at = align_up(2 * sizeof(int32_t) * BH, 256);
     Stage stage;
     std::unique_ptr<char[]> plain_read, plain_tables;
-    if (tables_at <= Stage::kBytes) st = hip_status(stage.take(), "staging memory");
-    if (st) return st;
+    if (tables_at <= Stage::kBytes) stage.take();
     const bool staged = stage.data() != nullptr;
     if (!staged) st = plain_memory(tables_at, &plain_read);
     if (st) return st;

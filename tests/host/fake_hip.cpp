@@ -22,6 +22,7 @@ struct Counts {
 } counts;
 size_t live_bytes = 0;
 bool pin_fails = false;
+thread_local hipError_t last_error = hipSuccess;
 int fail_wait = 0;              // which of the next stream waits fails (1: the next)
 const void* last_host = nullptr;  // where the last k_budgets wrote for the host
 void (*on_budgets)() = nullptr;
@@ -51,7 +52,7 @@ hipError_t hipHostMalloc(void** p, size_t bytes, unsigned int) {
     std::lock_guard<std::mutex> lock(mu);
     ++counts.mallocs;
     unsafe();
-    if (pin_fails) return hipErrorOutOfMemory;
+    if (pin_fails) return last_error = hipErrorOutOfMemory;
     *p = std::malloc(bytes + 16);
     *static_cast<size_t*>(*p) = bytes;
     *p = static_cast<char*>(*p) + 16;
@@ -59,6 +60,11 @@ hipError_t hipHostMalloc(void** p, size_t bytes, unsigned int) {
     live_bytes += bytes;
     counts.max_live = std::max(counts.max_live, (long)live.size());
     return hipSuccess;
+}
+hipError_t hipGetLastError() {
+    const hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
 }
 hipError_t hipHostFree(void* p) {
     std::lock_guard<std::mutex> lock(mu);
@@ -126,7 +132,7 @@ int launch_budgets(const LayerDev& L, const Shape& s, const uint8_t*, const int3
     }
     last_host = host;
     if (on_budgets) on_budgets();
-    return 0;
+    return (int)hipGetLastError();  // as the kernels' launchers do
 }
 int launch_tables(const LayerDev& L, const Shape& s, const LayoutTables& t, void*) {
     std::copy(t.seg_off, t.seg_off + s.BH, L.seg_off);

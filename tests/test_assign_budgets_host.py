@@ -196,3 +196,16 @@ def test_buffer_of_a_stream_not_waited_for_is_not_used_again(fake, waits):
         assert fake.fake_last_host() != lost
     g.assign()
     assert fake.fake_counts().frees == 0
+
+
+def test_without_pinned_memory(fake):
+    # no pinned memory to be had: the call copies, and pins once there is
+    h = Handle(64)
+    fake.fake_pin_fails(1)
+    assert h.size()[0] == B.HEADKV_ERR_CAPACITY
+    h.assign()
+    assert fake.fake_counts().copies == 2 + 7
+    fake.fake_pin_fails(0)
+    Handle(64).assign()
+    c = fake.fake_counts()
+    assert (c.copies, c.live_buffers) == (2 + 7, 1)
