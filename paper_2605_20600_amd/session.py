@@ -64,7 +64,10 @@ class Session:
     def stream() -> int:
         # torch.cuda.current_stream().cuda_stream without its Stream object: 0.2
         # us instead of 2.9, of the 5 us that a small launch takes
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:  # private functions, which a torch may not have
+            return torch.cuda.current_stream().cuda_stream
 
     def close(self):
         if self.h:
