@@ -26,6 +26,7 @@ thread_local hipError_t last_error = hipSuccess;
 int fail_wait = 0;              // which of the next stream waits fails (1: the next)
 const void* last_host = nullptr;  // where the last k_budgets wrote for the host
 void (*on_budgets)() = nullptr;
+headkv::AttnPlan last_plan{};  // of the last attention launch
 thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 
 void unsafe() {  // refused by the runtime while any thread captures in global mode
@@ -46,6 +47,11 @@ Counts fake_counts() {
 void fake_pin_fails(int yes) { pin_fails = yes != 0; }
 void fake_fail_wait(int n) { fail_wait = n; }
 const void* fake_last_host() { return last_host; }
+int fake_plan(int* tpr, int* items) {  // its threads
+    *tpr = last_plan.tpr;
+    *items = last_plan.items;
+    return last_plan.threads;
+}
 void fake_on_budgets(void (*f)()) { on_budgets = f; }
 
 hipError_t hipHostMalloc(void** p, size_t bytes, unsigned int) {
@@ -156,7 +162,8 @@ int launch_attn_layers(const LayersArg&, int, const MetaLayout&, const Shape&, i
     return 0;
 }
 int launch_attn(const LayerDev&, const Shape&, const AppendArgs&, const uint16_t*, float*,
-                uint64_t*, const AttnPlan&, void*, void*, void*) {
+                uint64_t*, const AttnPlan& p, void*, void*, void*) {
+    last_plan = p;
     return 0;
 }
 int launch_zero_words(uint64_t*, size_t, void*) { return 0; }

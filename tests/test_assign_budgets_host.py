@@ -55,20 +55,20 @@ def _buffer(n):
 class Handle:
     """A one-layer handle at its grouping step (group_threshold 1)."""
 
-    def __init__(self, batch, strategy=B.HEADKV_ATTN_VARLEN):
+    def __init__(self, batch, strategy=B.HEADKV_ATTN_VARLEN, heads=8, d=64):
         self.cfg = B.HeadKVConfig(
-            batch=batch, num_layers=1, num_heads=8, head_dim=64, prefix_len=0, row_len=10,
+            batch=batch, num_layers=1, num_heads=heads, head_dim=d, prefix_len=0, row_len=10,
             num_visual=N, recent_len=20, local_window=20, period=1, group_threshold=1,
             budget_mode=B.HEADKV_BUDGET_OVERRIDE, rho_num=1, rho_den=2, rs_num=1, rs_den=2,
             attn_strategy=strategy, score_mode=0, cfg_pairs=0, tau=0.9)
-        self.BH = 8 * batch
+        self.BH = heads * batch
         self.sizes = B.headkv_plan(self.cfg)
         self.dense, self.meta, self.ws = (_buffer(n) for n in self.sizes)
         self.h = B.headkv_create(self.cfg, [self.dense.ctypes.data], [self.meta.ctypes.data],
                                  self.ws.ctypes.data)
         B.headkv_prefill(self.h, 0, None, None)
-        row = _buffer(self.BH * 64 * 2).ctypes.data
-        B.headkv_append_and_evict(self.h, 0, 0, row, row, row)
+        self.row = _buffer(self.BH * d * 2)
+        B.headkv_append_and_evict(self.h, 0, 0, *(3 * [self.row.ctypes.data]))
         self.labels = np.zeros(self.BH, np.uint8)
         self.budgets = np.zeros(self.BH, np.int32)
         rng = np.random.default_rng(batch)
@@ -102,11 +102,14 @@ class Handle:
         take(np.int32, BH)  # n*
         take(np.int32, BH)  # labels
         order = take(np.int32, BH)
-        # room for every head at its largest, in chunks of 256 tokens
-        items, item_start = take(np.uint32, BH * ((N + 1 + 255) // 256)), take(np.int32, BH + 1)
+        # room for every head at its largest, in passes of 256 threads
+        d = self.cfg.head_dim
+        tokens = 256 // (d // 8) * 8
+        items = take(np.uint32, BH * ((N + 1 + tokens - 1) // tokens))
+        item_start = take(np.int32, BH + 1)
         want_cap = np.minimum(self.override + 1, N)
         assert (self.budgets == self.override).all() and (cap == want_cap).all()
-        seg = (2 * want_cap.astype(np.int64) * 64 * 2 + want_cap * 4 + 255) // 256 * 256
+        seg = (2 * want_cap.astype(np.int64) * d * 2 + want_cap * 4 + 255) // 256 * 256
         assert need == seg.sum() and (seg_off == np.cumsum(seg) - seg).all()
         if self.cfg.attn_strategy == B.HEADKV_ATTN_GROUPED:
             assert (order == np.argsort(self.override & 1, kind="stable")).all()
@@ -209,3 +212,26 @@ def test_without_pinned_memory(fake):
     Handle(64).assign()
     c = fake.fake_counts()
     assert (c.copies, c.live_buffers) == (2 + 7, 1)
+
+
+@pytest.mark.parametrize("heads,tokens,d,plan", [
+    # tokens of the largest head and of the others; threads, tokens per row, chunks
+    (4, (4501, 4501), 128, (256, 8, 4 * 36)),     # at most one chunk per compute unit
+    (64, (512, 512), 128, (256, 8, 256)),
+    (64, (513, 512), 128, (512, 8, 65 * 2 - 1)),  # 257 of 128 tokens
+    (128, (513, 512), 128, (1024, 8, 129)),
+    (200, (560, 560), 128, (1024, 9, 200)),       # one wide chunk each, two ordinary ones
+    (110, (1100, 1100), 128, (1024, 9, 220)),
+    (110, (2150, 2150), 64, (1024, 9, 220)),
+    (250, (520, 511), 64, (512, 8, 251)),
+    (160, (600, 600), 128, (512, 8, 480))])       # more than one per unit at every size
+def test_chunk_pass_rule(fake, heads, tokens, d, plan):
+    h = Handle(1, heads=heads, d=d)
+    # a table is cut for budget + period + the appended token
+    h.override[:] = tokens[1] - 2
+    h.override[0] = tokens[0] - 2
+    h.assign()
+    B.headkv_decode_attn(h.h, 0, h.row.ctypes.data, h.row.ctypes.data)
+    tpr, items = ctypes.c_int(), ctypes.c_int()
+    threads = fake.fake_plan(ctypes.byref(tpr), ctypes.byref(items))
+    assert (threads, tpr.value, items.value) == plan

@@ -193,6 +193,13 @@ def test_lumina1024_override_split_heads():
     _run_and_check(wl, [0, 31], [(0, 0), (31, 3)], _steps(wl, extra=(2000, 3000)))
 
 
+def test_lumina1024_wide_chunks():
+    # a layer whose chunk table is cut for the wide pass (238 chunks; 266 of the
+    # ordinary one), a slice of which 12 heads have chunks of more than 512 tokens
+    wl = W.LUMINA1024
+    _run_and_check(wl, [1], [(1, 2)], _steps(wl, extra=(2000,)))
+
+
 def test_stress_update_every_step():
     wl = W.STRESS
     _run_and_check(wl, [0], [(0, 0), (0, 63)], _steps(wl, extra=(310, 1500)))
