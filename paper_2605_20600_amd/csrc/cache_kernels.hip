@@ -66,14 +66,16 @@ struct ScoreLds {
 
 // One block per head.  The normaliser and the backward mass are sums whose
 // order decides n*, so one thread adds each of them in order: the launch is
-// bound by those two chains of len dependent fp64 additions (3.2 and 4.4
-// of 15 us at 428 tokens) and by the round trips before them.  The reads of a chain go
+// bound by those two chains of len dependent fp64 additions (3.2 and 4.4 us
+// at 428 tokens) and by the round trips before them.  The reads of a chain go
 // out kScoreRun values ahead of their additions (read one by one, each behind
 // the LDS, the chains took three quarters of the launch), and the key rows
 // arrive in LDS as whole rows, all of a tile's loads in flight at once, R rows
 // per thread, so that a query value read from LDS serves R rows (read by the
 // threads from memory, 16 bytes of 64 rows at a time, one round trip each).
-// 256 heads of 428 tokens, d = 128: 41.3 -> 17 us.
+// Launches one after the other, before and now: 256 heads of 428 tokens, d =
+// 128, 39.9 -> 15.5 us (42.5 and 18.6 in a profiler's trace of single ones);
+// 2,048 such heads 96 -> 72; 4 heads of 6,656 tokens 512 -> 166.
 template <int D, int R>
 __global__ __launch_bounds__(kBlock) void k_score(LayerDev L, const uint16_t* q, int32_t* n_star,
                                                   uint8_t* is_local, int len, double sqrt_d,

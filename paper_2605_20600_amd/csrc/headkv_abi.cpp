@@ -158,7 +158,7 @@ Plan make_plan(const headkv_config& c) {
     // and its window starts at step 0 either way)
     p.ml.compute(p.BH, c.head_dim, p.BH * per_head, std::min(c.period, c.num_visual),
                  c.score_mode == HEADKV_SCORE_ATTN_SUM ? 1 : 0);
-    // partial (max, sum, weighted V) of every chunk table entry
+    // merge words (d of 64 bits) of every chunk table entry
     p.ws_bytes = align_up((size_t)p.BH * per_head * c.head_dim * sizeof(uint64_t), 256);
     return p;
 }
@@ -174,7 +174,10 @@ struct ChunkPass {
 // costs less than the longer pass: 32 heads of 250-450 tokens, d = 128, 256 /
 // 512 / 1024 threads 5.21 / 5.61 / 6.92 us per launch; 128 such heads, 7.73 /
 // 7.11 / 7.69, the 512-thread table is the smallest that fits; 4 heads 4.79 /
-// 5.22 / 6.25).  With more chunks than CUs at every size, the largest block's
+// 5.22 / 6.25).  It holds for few heads with long caches too, in spite of the
+// deeper merge; d = 128, the largest block that fills the CUs (chosen before)
+// and the smallest that fits: 4 heads of 2,128 / 4,528 / 6,448 tokens 6.92 ->
+// 5.98, 8.48 -> 6.74 and 9.09 -> 6.85 us, 16 heads of 2,128 7.69 -> 7.01.  With more chunks than CUs at every size, the largest block's
 // wide pass if its fewer chunks then fit (Lumina-1024: 128 heads of 1 to 16
 // rows, in most layers 230-250 chunks of 576 tokens, else 460 of 256: 10.92 ->
 // 10.68 us per launch over all layers, whole job +2.1 %); else the fewest

@@ -6,9 +6,10 @@
 // A block of W wavefronts takes W * 32 queries of one head, 32 each.  The keys
 // arrive in tiles of KT = 32 * SUBS: the K and V rows of the next tile go from
 // memory straight into LDS (global_load_lds, 16 bytes per lane) while the
-// current one is used, one barrier per tile.  The rows of a tile lie unpadded in LDS, their 16-byte
-// pieces permuted within the row (swizzle below) so that both operand reads
-// are free of bank conflicts.  For each tile a wavefront computes
+// current one is used, one barrier per tile.  The rows of a tile lie unpadded in
+// LDS, their 16-byte pieces permuted within the row (swizzle in device_common.h)
+// so that both operand reads are free of bank conflicts.  For each tile a
+// wavefront computes
 //   S^T = K_tile Q^T   32x32x16 bf16 MFMAs over d (A = key rows from LDS, B =
 //                      the wavefront's query rows, held in registers), so
 //                      that a lane holds 16 of the 32 scores of one query and
@@ -25,15 +26,15 @@
 // launch stores the prefix keys and values into the cache (headkv_prefill):
 // each block writes the rows of its own queries from the tiles in LDS.
 //
-// Long prefixes are bound inside the CU (C = 2048, 64 heads of 128: 29 % of the
-// matrix cores' cycles, 44 % of the vector ALU's issue, no LDS bank conflicts;
+// Long prefixes are bound inside the CU (C = 2048, 64 heads of 128: 30 % of the
+// matrix cores' cycles, 45 % of the vector ALU's issue, no LDS bank conflicts;
 // without the loads of the tiles it would take 24 % less, without the
-// exponentials 6 %), short ones by their bytes.  Per launch, with the tiles
-// staged through registers, V read four 2-byte elements at a time, 32x32x8
-// steps and everything written through the L2, and now: C = 2048, 64 heads of
-// 128 492 -> 100 us (690 TFLOP/s of causal products); C = 300, 320 heads of 64
-// 38.8 -> 17.6 us; C = 128, 256 heads of 128 18.4 -> 10.9 us; C = 64, 512 heads
-// of 128 20.3 -> 10.4 us (5.7 TB/s).
+// exponentials 6 %), short ones by their bytes.  Per launch, one after the other
+// on several layers' buffers, with the tiles staged through registers, V read
+// four 2-byte elements at a time, 32x32x8 steps and everything written through
+// the L2, and now: C = 2048, 64 heads of 128 492 -> 103 us (670 TFLOP/s of causal
+// products); C = 300, 320 heads of 64 38.8 -> 17.6 us; C = 128, 256 heads of 128
+// 18.4 -> 10.9 us; C = 64, 512 heads of 128 20.3 -> 10.4 us (5.7 TB/s).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
